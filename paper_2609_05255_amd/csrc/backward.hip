@@ -96,9 +96,13 @@ struct GeoGrad {
     float dls[3];
     float dq[4];
     float dlogit;
+    float dmean2d[2];
 };
 
-// Derivative of the geometry part of the preprocess (everything except colour).
+// Derivative of the geometry part of the preprocess (everything except colour),
+// from the moments of dL/dpower in g9[0..5] (kAccStride): with the conic
+// (a, b, c), dL/dmean2d = (a m_x + b m_y, c m_y + b m_x), dL/d(a, b, c) =
+// -(m_xx / 2, m_xy, m_yy / 2), and o dL/do = m_0 (below the cap alpha = o G).
 __device__ __forceinline__ void geometry_bwd(const Cam& c, const float mu[3], const float ls[3], const float qraw[4],
                                              float logit, const float* g9, GeoGrad& out)
 {
@@ -138,10 +142,13 @@ __device__ __forceinline__ void geometry_bwd(const Cam& c, const float mu[3], co
     const float A = TS[0] * T[0] + TS[1] * T[1] + TS[2] * T[2] + 0.3f;
     const float B = TS[0] * T[3] + TS[1] * T[4] + TS[2] * T[5];
     const float C = TS[3] * T[3] + TS[4] * T[4] + TS[5] * T[5] + 0.3f;
-    const float idet = 1.f / (A * C - B * B);
+    // A C - B^2 with the product's rounding error added back: it cancels for
+    // long thin splats
+    const float BB = B * B;
+    const float idet = 1.f / (__fmaf_rn(A, C, -BB) + __fmaf_rn(-B, B, BB));
     const float qa = C * idet, qb = -B * idet, qc = A * idet;     // conic
     // dL/dcov = -Q GQ Q with GQ = [[da, db/2], [db/2, dc]]
-    const float ga = g9[2], gb = 0.5f * g9[3], gc = g9[4];
+    const float ga = -0.5f * g9[3], gb = -0.5f * g9[4], gc = -0.5f * g9[5];
     const float m00 = qa * ga + qb * gb, m01 = qa * gb + qb * gc;
     const float m10 = qb * ga + qc * gb, m11 = qb * gb + qc * gc;
     const float G00 = -(m00 * qa + m01 * qb), G01 = -(m00 * qb + m01 * qc);
@@ -168,9 +175,12 @@ __device__ __forceinline__ void geometry_bwd(const Cam& c, const float mu[3], co
     if (cly) dt[2] += c.fy * (uy * itz) * itz2 * dj12;
     else { dt[1] += -c.fy * itz2 * dj12; dt[2] += 2.f * c.fy * t[1] * itz2 * itz * dj12; }
     // projected mean px = fx tx / tz + cx
-    dt[0] += c.fx * itz * g9[0];
-    dt[1] += c.fy * itz * g9[1];
-    dt[2] += -(c.fx * t[0] * g9[0] + c.fy * t[1] * g9[1]) * itz2;
+    const float dmx = qa * g9[1] + qb * g9[2], dmy = qc * g9[2] + qb * g9[1];
+    out.dmean2d[0] = dmx;
+    out.dmean2d[1] = dmy;
+    dt[0] += c.fx * itz * dmx;
+    dt[1] += c.fy * itz * dmy;
+    dt[2] += -(c.fx * t[0] * dmx + c.fy * t[1] * dmy) * itz2;
     for (int k = 0; k < 3; ++k) out.dmu[k] = V[k] * dt[0] + V[4 + k] * dt[1] + V[8 + k] * dt[2];
     // Sigma = M M^T: dM = 2 dS M (dS symmetric)
     float dR[9];
@@ -194,8 +204,7 @@ __device__ __forceinline__ void geometry_bwd(const Cam& c, const float mu[3], co
     out.dq[1] = (dqn[1] - x * qd) * iqn;
     out.dq[2] = (dqn[2] - y * qd) * iqn;
     out.dq[3] = (dqn[3] - z * qd) * iqn;
-    const float o = 1.f / (1.f + __expf(-logit));
-    out.dlogit = g9[5] * o * (1.f - o);
+    out.dlogit = g9[0] / (1.f + __expf(logit));   // m_0 (1 - o)
 }
 
 __device__ __forceinline__ void write_zero_grads(const BwdArgs& a, int i)
@@ -221,7 +230,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3(BwdArgs a)
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
-    gg.dlogit = 0.f;
+    gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
     float g9[kAccStride];
     for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
     float Y[16], gc[3] = {0.f, 0.f, 0.f};
@@ -283,8 +292,8 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3(BwdArgs a)
     for (int j = 0; j < 4; ++j) __builtin_nontemporal_store(gg.dq[j], &a.dquats[j * n + i]);
     __builtin_nontemporal_store(gg.dlogit, &a.dlogits[i]);
     if (a.dmean2d) {
-        __builtin_nontemporal_store(g9[0], &a.dmean2d[i]);
-        __builtin_nontemporal_store(g9[1], &a.dmean2d[n + i]);
+        __builtin_nontemporal_store(gg.dmean2d[0], &a.dmean2d[i]);
+        __builtin_nontemporal_store(gg.dmean2d[1], &a.dmean2d[n + i]);
     }
 }
 
@@ -303,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3_adam(BwdArgs a, A
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
-    gg.dlogit = 0.f;
+    gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
     float g9[kAccStride];
     for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
     float Y[16], gc[3] = {0.f, 0.f, 0.f}, dY[16];
@@ -380,8 +389,8 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3_adam(BwdArgs a, A
                             gg.dq[0], gg.dq[1], gg.dq[2], gg.dq[3], gg.dlogit};
     adam_apply(f, tg, rg, n, i, pg, gg11);
     if (a.dmean2d) {
-        __builtin_nontemporal_store(g9[0], &a.dmean2d[i]);
-        __builtin_nontemporal_store(g9[1], &a.dmean2d[n + i]);
+        __builtin_nontemporal_store(gg.dmean2d[0], &a.dmean2d[i]);
+        __builtin_nontemporal_store(gg.dmean2d[1], &a.dmean2d[n + i]);
     }
 }
 
@@ -401,7 +410,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_lobe(BwdArgs a)
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
-    gg.dlogit = 0.f;
+    gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
     float g9[kAccStride];
     for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
     float gc[3] = {0.f, 0.f, 0.f}, dl[kRows];
@@ -452,8 +461,8 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_lobe(BwdArgs a)
     for (int j = 0; j < 4; ++j) __builtin_nontemporal_store(gg.dq[j], &a.dquats[j * n + i]);
     __builtin_nontemporal_store(gg.dlogit, &a.dlogits[i]);
     if (a.dmean2d) {
-        __builtin_nontemporal_store(g9[0], &a.dmean2d[i]);
-        __builtin_nontemporal_store(g9[1], &a.dmean2d[n + i]);
+        __builtin_nontemporal_store(gg.dmean2d[0], &a.dmean2d[i]);
+        __builtin_nontemporal_store(gg.dmean2d[1], &a.dmean2d[n + i]);
     }
 }
 
@@ -560,7 +569,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_preprocess_bwd_latent(BwdArgs a)
             for (int j = 0; j < 3; ++j) { a.dmeans[j * n + i] = gg.dmu[j]; a.dlog_scales[j * n + i] = gg.dls[j]; }
             for (int j = 0; j < 4; ++j) a.dquats[j * n + i] = gg.dq[j];
             a.dlogits[i] = gg.dlogit;
-            if (a.dmean2d) { a.dmean2d[i] = g9[0]; a.dmean2d[n + i] = g9[1]; }
+            if (a.dmean2d) { a.dmean2d[i] = gg.dmean2d[0]; a.dmean2d[n + i] = gg.dmean2d[1]; }
         }
         wave_lds_sync();   // st.dd is read before the next chunk restages
     }
@@ -728,7 +737,7 @@ __global__ __launch_bounds__(kBlock, kW == 32 ? 2 : 3) void k_preprocess_bwd_neu
             for (int j = 0; j < 3; ++j) { a.dmeans[j * n + i] = gg.dmu[j]; a.dlog_scales[j * n + i] = gg.dls[j]; }
             for (int j = 0; j < 4; ++j) a.dquats[j * n + i] = gg.dq[j];
             a.dlogits[i] = gg.dlogit;
-            if (a.dmean2d) { a.dmean2d[i] = g9[0]; a.dmean2d[n + i] = g9[1]; }
+            if (a.dmean2d) { a.dmean2d[i] = gg.dmean2d[0]; a.dmean2d[n + i] = gg.dmean2d[1]; }
         }
         if (resid) wave_lds_sync();   // the stage is read before the next chunk restages
     }

@@ -8,7 +8,9 @@
 // against the wave's pixels, the batch is staged in the wave's own LDS slot,
 // and each splat that passes is then read back by the whole wave from one
 // address (a broadcast read). No workgroup barriers; a wave stops when its own
-// pixels are done.
+// pixels are done. The forward takes 0.155 ms on the 3M-Gaussian 1600x1064 scene
+// (0.182 ms before the alpha test moved to logarithms, the constants to the
+// staging lane and the end-of-walk test to scalar lane masks).
 //
 // Workgroup ids are mapped to tiles so that each XCD (workgroups are dealt
 // round-robin over the 8 XCDs) renders a contiguous band of tiles, whose lists
@@ -40,53 +42,136 @@ __device__ __forceinline__ int tile_of_block(int block, int n_tiles)
 
 inline int blend_grid(int n_tiles) { return (int)div_up(n_tiles, kXcds) * kXcds; }
 
-constexpr float kAlphaMin = 1.0f / 255.0f;
+constexpr float kPowerMargin = 1e-3f;   // of gs_splat.power_min below -ln(255 opacity)
 constexpr float kAlphaMax = 0.99f;
 constexpr float kTMin = 0.0001f;
 constexpr float kLog2e = 1.4426950408889634f;
 
 
-// One splat record in registers (the fields the blend needs).
-struct SplatReg {
-    float mx, my, ca, cb, cc, op, r, g, b, pmin, ex, ey;
-    uint32_t id;
+// A splat as the walks read it from LDS: the record with the constants of the
+// quadratic form taken once by the lane that stages it. In base-2 units (times
+// log2 e), so that exp(power) is one hardware exp2: -power log2 e = ka dx^2 +
+// kb dx dy + kc dy^2. e_max is its bound where alpha reaches 1/255,
+// log2(255 opacity), from power_min less its margin.
+struct Staged {
+    float mx, my, ka, kb, kc, op, r, g, b, e_max;
 };
 
-// power(dy) = -(a dx^2 + c dy^2)/2 - b dx dy for one column, in base-2 units
-// (times log2 e) so that exp(power) is one hardware exp2:
-// power log2 e = q0 + dy (q1 + dy q2).
-struct Quad {
-    float q0, q1, q2;
-};
-
-__device__ __forceinline__ Quad column_quad(const SplatReg& s, float dx)
+__device__ __forceinline__ void stage_words(const float4& c0, const float4& c1, const float4& c2, float4& w0,
+                                            float4& w1, float2& w2)
 {
-    Quad q;
-    q.q0 = (-0.5f * kLog2e) * s.ca * dx * dx;
-    q.q1 = (-kLog2e * dx) * s.cb;
-    q.q2 = (-0.5f * kLog2e) * s.cc;
-    return q;
+    w0 = make_float4(c0.x, c0.y, (0.5f * kLog2e) * c0.z, kLog2e * c0.w);
+    w1 = make_float4((0.5f * kLog2e) * c1.x, c1.y, c1.z, c1.w);
+    const float reach = -kLog2e * (c2.y + kPowerMargin);
+    w2 = make_float2(c2.x, reach > 0.f ? reach : 0.f);
 }
 
-__device__ __forceinline__ float quad_power(const Quad& q, float dy)
+__device__ __forceinline__ Staged staged(const float4& w0, const float4& w1, const float2& w2)
 {
-    return __fmaf_rn(__fmaf_rn(q.q2, dy, q.q1), dy, q.q0);
+    return Staged{w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y};
+}
+
+// A wave's staged batch: three planes at one 16-byte stride, so that a splat's
+// reads share one address register.
+struct StageSlot {
+    float4 w[3][kWave];
+    __device__ __forceinline__ float2& tail(int j) { return reinterpret_cast<float2&>(w[2][j]); }
+};
+
+// -power log2 e of one column as a polynomial in dy: q0 + dy (q1 + dy kc).
+struct Quad {
+    float q0, q1;
+};
+
+__device__ __forceinline__ Quad column_quad(const Staged& s, float dx) { return Quad{s.ka * dx * dx, s.kb * dx}; }
+
+__device__ __forceinline__ float quad_neg_power(const Staged& s, const Quad& q, float dy)
+{
+    return __fmaf_rn(__fmaf_rn(s.kc, dy, q.q1), dy, q.q0);
+}
+
+// power <= 0 and alpha >= 1/255 (o e^power >= 1/255, on the logarithms) as one
+// unsigned comparison of bit patterns: e = -power log2 e and its bound are
+// non-negative where the test passes, so their bits order as their values; a
+// negative e (power > 0) or a NaN has larger bits than any bound. e is never
+// -0 (a > 0, so q0 is +0 or more, and sums that cancel round to +0), nor is the
+// bound. Taken on the logarithm the alpha test needs no exponential, and the
+// pixels that pass need no second test: 2 vector instructions fewer per pixel.
+__device__ __forceinline__ bool in_reach(float e, float e_max)
+{
+    return __float_as_uint(e) <= __float_as_uint(e_max);
 }
 
 template <int kCtrl>
 __device__ __forceinline__ float dpp_f32(float v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xF, 0xF, true));
 }
 
-// Sum over the 16 lanes of each row, in every lane of the row.
-__device__ __forceinline__ float row_sum(float v)
+// a's sum over the lane halves in lanes 0..31, b's in lanes 32..63 (each lane
+// with its partner 32 lanes away), and the same for odd and even rows of 16.
+__device__ __forceinline__ float merge32(float a, float b)
 {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false));
-    return v;
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+__device__ __forceinline__ float merge16(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Wave sums of one splat's nine accumulator entries (kAccStride) from its six
+// per-lane sums over the lane's pixels: p0, p1, p2 (dL/dpower times 1, dy, dy^2)
+// and the colour gradient c. dx is the same in the four lanes of a column, so
+// the four rows of 16 lanes are added first, two values merged per lane swap,
+// and the moments in dx are products of the column sums. Within the rows, DPP
+// sums take two registers (8 lanes each) and a third (every other quad) at
+// once. The sum of entry e ends in lane reduce_src_lane(e); one LDS permute
+// brings the nine into the first lanes, so that their atomics stay one request
+// per 64 bytes (from four rows they are four, which at 3M Gaussians costs
+// 0.09 ms). 23 vector instructions, where a butterfly of selects and permutes
+// over nine values took 46. Every lane of the wave must call it (a disabled
+// DPP source lane reads 0).
+__device__ __forceinline__ float wave_reduce9(float p0, float p1, float p2, float c0, float c1, float c2, float dx,
+                                              bool odd_row, bool hi8, bool odd4, int src_byte)
+{
+    const float s1 = merge16(merge32(p0, p1), merge32(c0, c1));   // rows: p0, c0, p1, c1
+    const float pc = merge32(p2, c2);
+    const float r1 = merge16(pc, pc);                             // rows: p2, p2, c2, c2
+    const float dx1 = dx * s1;
+    const float s2 = odd_row ? r1 : dx1;                          // rows: p0 dx, p2, p1 dx, c2
+    const float s3 = dx * dx1;                                    // row 0: p0 dx^2
+    const float h1 = s1 + dpp_f32<0x128>(s1), h2 = s2 + dpp_f32<0x128>(s2), h3 = s3 + dpp_f32<0x128>(s3);   // row_ror:8
+    const float h = hi8 ? h2 : h1;
+    // both sums before the select: a select over the sums' own code would become
+    // a branch that disables half of the source lanes
+    const float m = h + dpp_f32<0x141>(h), m3 = h3 + dpp_f32<0x141>(h3);      // row_half_mirror
+    const float q = odd4 ? m3 : m;
+    const float t = q + dpp_f32<0xB1>(q);                                     // quad_perm, lane ^ 1
+    const float u = t + dpp_f32<0x4E>(t);                                     // lane ^ 2
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(src_byte, __float_as_int(u)));
+}
+
+// row[lane] += v with a wave-uniform row: its address is kept in scalar
+// registers (folded into the lane's, it is a 64-bit vector multiply-add).
+__device__ __forceinline__ void add_scalar_row(float* row, int lane, float v)
+{
+    uint64_t base = reinterpret_cast<uint64_t>(row);
+    asm("" : "+s"(base));
+    auto* p = reinterpret_cast<__attribute__((address_space(1))) float*>(base);
+    __hip_atomic_fetch_add(p + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The lane whose sum is entry e: M0, Mx, My, Mxx, Mxy, Myy, c0, c1, c2.
+__device__ __forceinline__ int reduce_src_lane(int e)
+{
+    constexpr int src[kAccStride] = {0, 8, 32, 4, 40, 24, 16, 48, 56};
+    int r = 0;
+#pragma unroll
+    for (int k = 0; k < kAccStride; ++k) r = e == k ? src[k] : r;
+    return r;
 }
 
 // Whether the splat's alpha >= 1/255 region (power >= power_min, i.e. the
@@ -153,14 +238,14 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_fwd(Cam cam, con
         py[k] = (float)(y0 + kRowStep * k) + 0.5f;
         T[k] = (x < cam.width && (y0 + kRowStep * k) < cam.height) ? 1.f : -1.f;
     }
-    bool any = false;
+    uint64_t alive = 0;   // lanes with a pixel still blending
 #pragma unroll
-    for (int k = 0; k < kPix; ++k) any = any || T[k] > 0.f;
+    for (int k = 0; k < kPix; ++k) alive |= __ballot(T[k] > 0.f);
     // each batch of 64 list entries is staged in LDS; the wave then reads one
     // record per step at a uniform address (a broadcast read: no vector
     // instructions, unlike a lane-by-lane readlane broadcast)
-    __shared__ float4 stage[kTile * kTile / kPix / kWave][3][kWave];
-    float4 (*st)[kWave] = stage[wave];
+    __shared__ StageSlot stage[kTile * kTile / kPix / kWave];
+    StageSlot& st = stage[wave];
     float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0, c2 = c0;
     if (start + lane < end) {
         const float4* p = reinterpret_cast<const float4*>(splats + values[start + lane]);
@@ -168,8 +253,8 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_fwd(Cam cam, con
     }
     // the list entry of the batch after the prefetched one, loaded a batch early
     uint32_t nid = start + kWave + lane < end ? values[start + kWave + lane] : 0u;
-    for (uint32_t b = start; b < end && __ballot(any) != 0; b += kWave) {
-        st[0][lane] = c0; st[1][lane] = c1; st[2][lane] = c2;
+    for (uint32_t b = start; b < end && alive != 0; b += kWave) {
+        stage_words(c0, c1, c2, st.w[0][lane], st.w[1][lane], st.tail(lane));
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -191,40 +276,31 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_fwd(Cam cam, con
         while (todo != 0) {
             const int j = (int)__builtin_ctzll(todo);
             todo &= todo - 1;
-            SplatReg s;
-            const float4 w0 = st[0][j], w1 = st[1][j], w2 = st[2][j];
-            s.mx = w0.x; s.my = w0.y;
-            s.ca = w0.z; s.cb = w0.w; s.cc = w1.x; s.op = w1.y; s.r = w1.z; s.g = w1.w; s.b = w2.x; s.pmin = w2.y;
+            const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
             const float dx = px - s.mx;
             const Quad q = column_quad(s, dx);
-            const float pmin2 = s.pmin * kLog2e;
+            alive = 0;
 #pragma unroll
             for (int k = 0; k < kPix; ++k) {
-                // one branch per pixel; the alpha floor and the stop rule are
-                // selects inside it (the same decisions, fewer exec-mask changes)
-                const float power2 = quad_power(q, py[k] - s.my);
-                if (T[k] > 0.f && power2 <= 0.f && power2 >= pmin2) {
-                    const float alpha = fminf(kAlphaMax, s.op * __builtin_amdgcn_exp2f(power2));
+                // one branch per pixel; the stop rule is a select inside it
+                const float e = quad_neg_power(s, q, py[k] - s.my);
+                const bool on = T[k] > 0.f;
+                alive |= __ballot(on);
+                if (on & in_reach(e, s.e_max)) {
+                    const float alpha = fminf(kAlphaMax, s.op * __builtin_amdgcn_exp2f(-e));
                     const float Tn = T[k] * (1.f - alpha);
-                    const bool on = alpha >= kAlphaMin;
-                    const bool stop = on && Tn < kTMin;
-                    const bool blend = on && !stop;
-                    const float w = blend ? alpha * T[k] : 0.f;
+                    const bool stop = Tn < kTMin;
+                    const float w = stop ? 0.f : alpha * T[k];
                     C0[k] = __fmaf_rn(s.r, w, C0[k]);
                     C1[k] = __fmaf_rn(s.g, w, C1[k]);
                     C2[k] = __fmaf_rn(s.b, w, C2[k]);
-                    last[k] = blend ? b - start + (uint32_t)j + 1 : last[k];
-                    T[k] = stop ? -T[k] : (blend ? Tn : T[k]);
+                    last[k] = stop ? last[k] : b - start + (uint32_t)j + 1;
+                    T[k] = stop ? -T[k] : Tn;
                 }
             }
-            // a pixel can only stop on a splat that reaches it. T > 0 is tested
-            // on its bits (T is never NaN): an integer maximum, where a float
-            // one would first be canonicalised
-            int tmax = __float_as_int(T[0]);
-#pragma unroll
-            for (int k = 1; k < kPix; ++k) tmax = max(tmax, __float_as_int(T[k]));
-            any = tmax > 0;
-            if (__ballot(any) == 0) break;
+            // no pixel was still blending before this splat (found one visit late:
+            // the comparisons are those of the branches above)
+            if (alive == 0) break;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -257,12 +333,22 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
 
 // ---- backward -----------------------------------------------------------------
 // Per pixel, back to front from its last blended splat, with T recovered as
-// T_i = T_{i+1} / (1 - alpha_i) and S the suffix sum of colour * alpha * T plus
-// T_final * bg:  dL/dcolour_i = alpha_i T_i g,  dL/dalpha_i = sum_ch
-// (T_i c_i - S / (1 - alpha_i)) g_ch. The alpha and skip decisions reuse the
-// forward's code, so the same splats are found contributing. Each lane sums
-// its pixels, the wave sums its lanes, and lane 63 issues one set of float
-// atomics per (wave, splat).
+// T_i = T_{i+1} / (1 - alpha_i) and A the composited colour behind the splat,
+// projected on the upstream gradient g (A_i = A_{i+1} + alpha_i (c_i . g -
+// A_{i+1}), the background at the back):  dL/dcolour_i = alpha_i T_i g,
+// dL/dalpha_i = T_i (c_i . g - A_{i+1}). The alpha and skip decisions reuse the
+// forward's code, so the same splats are found contributing. Each lane sums its
+// pixels' terms, the wave its lanes (wave_reduce9), and nine lanes issue one
+// set of float atomics per (wave, splat).
+//
+// Bound by vector instruction issue: on the 3M-Gaussian 1600x1064 scene it takes
+// 0.271 ms, of which its instructions alone (149M wave instructions at 4 cycles;
+// the two transcendentals per pixel take 16) fill 0.24 ms or more. What shortened it
+// (from 0.318 ms and 204M): raw moments summed per splat and combined once per
+// Gaussian later, no opacity sum (dL/dopacity follows from the first moment),
+// the recursion in A (no division beside T's), the alpha test on logarithms,
+// constants taken by the staging lane, lane masks combined as scalars, scalar
+// atomic addresses, and half the instructions of the reduction.
 
 template <int kPix>
 __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, const gs_splat* __restrict__ splats,
@@ -283,9 +369,6 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
     const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row_lane = lane & 15;
-    // lane bits of the butterfly reduction and the accumulator entry this lane adds
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-    const int entry = (row_lane & 8) ? 8 : 4 * (lane & 1) + 2 * ((lane >> 1) & 1) + ((lane >> 2) & 1);
     const int x = tx * kTile + row_lane;
     const int y0 = ty * kTile + 4 * kPix * wave + (lane >> 4);
     const float px = (float)x + 0.5f;
@@ -297,9 +380,9 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
     const float box_hi = box_lo + (float)(4 * kPix - 1);
     const float box_cy = 0.5f * (box_lo + box_hi), box_hy = 0.5f * (box_hi - box_lo);
 
-    // Sg: the suffix sum S projected on the pixel's upstream gradient g, the
-    // only form of S the gradient needs
-    float T[kPix], py[kPix], g0[kPix], g1[kPix], g2[kPix], Sg[kPix];
+    // A: the colour behind the current splat, as composited, projected on the
+    // pixel's upstream gradient g, the only form of it the gradient needs
+    float T[kPix], py[kPix], g0[kPix], g1[kPix], g2[kPix], A[kPix];
     uint32_t last[kPix];
     uint32_t stop = 0;
 #pragma unroll
@@ -317,19 +400,21 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
             g1[k] = dL_dimage[hw + pix];
             g2[k] = dL_dimage[2 * hw + pix];
         }
-        Sg[k] = T[k] * __fmaf_rn(cam.bg[2], g2[k], __fmaf_rn(cam.bg[1], g1[k], cam.bg[0] * g0[k]));
+        A[k] = __fmaf_rn(cam.bg[2], g2[k], __fmaf_rn(cam.bg[1], g1[k], cam.bg[0] * g0[k]));
         stop = max(stop, last[k]);
     }
     // list positions [0, stop) can contribute
     for (int o = 32; o > 0; o >>= 1) stop = max(stop, (uint32_t)__shfl_xor((int)stop, o));
+    stop = (uint32_t)__builtin_amdgcn_readfirstlane((int)stop);   // uniform: the walk's control stays scalar
     if (stop == 0) return;
     const int nbatch = (int)((stop + kWave - 1) / kWave);
     // each batch of 64 list entries is staged in LDS and read back one record
     // per step at a uniform address (broadcast), as in the forward
-    __shared__ float4 stage[kTile * kTile / kPix / kWave][3][kWave];
-    __shared__ uint32_t stage_id[kTile * kTile / kPix / kWave][kWave];
-    float4 (*st)[kWave] = stage[wave];
-    uint32_t* sid = stage_id[wave];
+    __shared__ StageSlot stage[kTile * kTile / kPix / kWave];
+    StageSlot& st = stage[wave];
+    // lane roles of the reduction (wave_reduce9); lanes 0..8 add one entry each
+    const bool red_row = lane & 16, red_hi8 = lane & 8, red_odd4 = lane & 4;
+    const int red_src = 4 * reduce_src_lane(lane);
     float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0, c2 = c0;
     uint32_t cid = 0, nid = 0;   // nid: the list entry of the batch after the prefetched one, loaded a batch early
     {
@@ -343,8 +428,8 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
     }
     for (int bi = nbatch - 1; bi >= 0; --bi) {
         const uint32_t b = (uint32_t)bi * kWave;
-        st[0][lane] = c0; st[1][lane] = c1; st[2][lane] = c2;
-        sid[lane] = cid;
+        stage_words(c0, c1, c2, st.w[0][lane], st.w[1][lane], st.tail(lane));
+        const uint32_t batch_id = cid;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -367,99 +452,46 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
             const int j = 63 - (int)__builtin_clzll(todo);
             todo ^= 1ull << j;
             const uint32_t pos = b + (uint32_t)j;
-            SplatReg s;
-            {
-                const float4 w0 = st[0][j], w1 = st[1][j], w2 = st[2][j];
-                s.mx = w0.x; s.my = w0.y; s.ca = w0.z; s.cb = w0.w;
-                s.cc = w1.x; s.op = w1.y; s.r = w1.z; s.g = w1.w;
-                s.b = w2.x; s.pmin = w2.y;
-                s.id = sid[j];
-            }
+            const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
             const float dx = px - s.mx;
             const Quad q = column_quad(s, dx);
-            const float pmin2 = s.pmin * kLog2e;
-            // per-lane sums over its pixels: colour gradient, opacity gradient, and
-            // dL/dpower times 1, dy, dy^2 (the lane's pixels share dx), from which
-            // the moments dpow dx, dpow dy, dpow dx^2, dpow dx dy, dpow dy^2 and
-            // then dmean2d and dconic follow once per splat
-            float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f, a_dop = 0.f;
+            // per-lane sums over its pixels: colour gradient and dL/dpower times
+            // 1, dy, dy^2 (the lane's pixels share dx)
+            float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f;
             float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-            bool any = false;
+            uint64_t any = 0;
 #pragma unroll
             for (int k = 0; k < kPix; ++k) {
-                // one branch per pixel; the alpha floor and the cap are selects
-                // inside it (the same decisions, fewer exec-mask changes)
+                // one branch per pixel (no short circuit); the cap is a select inside it
                 const float dy = py[k] - s.my;
-                const float power2 = quad_power(q, dy);
-                if (!(pos < last[k] && power2 <= 0.f && power2 >= pmin2)) continue;
-                const float G = __builtin_amdgcn_exp2f(power2);
-                const float oG = s.op * G;
-                const bool on = oG >= kAlphaMin;             // alpha >= 1/255
-                const float alpha = on ? fminf(kAlphaMax, oG) : 0.f;
-                any = any || on;
+                const float e = quad_neg_power(s, q, dy);
+                // the comparisons' lane masks, combined as scalars
+                const uint64_t reach = __ballot(pos < last[k]) & __ballot(in_reach(e, s.e_max));
+                any |= reach;
+                if (!__builtin_amdgcn_inverse_ballot_w64(reach)) continue;
+                const float oG = s.op * __builtin_amdgcn_exp2f(-e);
+                const float alpha = fminf(kAlphaMax, oG);
                 // hardware reciprocal (1 ulp): T is recovered over a few hundred
                 // splats, so its relative error stays near 1e-5
-                const float inv = __builtin_amdgcn_rcpf(1.f - alpha);
-                T[k] *= inv;                                // transmittance in front of this splat
+                T[k] *= __builtin_amdgcn_rcpf(1.f - alpha);   // transmittance in front of this splat
                 const float w = alpha * T[k];
                 a_c0 = __fmaf_rn(w, g0[k], a_c0);
                 a_c1 = __fmaf_rn(w, g1[k], a_c1);
                 a_c2 = __fmaf_rn(w, g2[k], a_c2);
-                const float cg = __fmaf_rn(s.b, g2[k], __fmaf_rn(s.g, g1[k], s.r * g0[k]));
-                const float dalpha = __fmaf_rn(T[k], cg, -inv * Sg[k]);
-                Sg[k] = __fmaf_rn(w, cg, Sg[k]);
-                // below the cap alpha = o G; capped (or skipped) entries pass nothing
-                const bool unc = on && oG < kAlphaMax;
-                a_dop = unc ? __fmaf_rn(G, dalpha, a_dop) : a_dop;
-                const float dpow = unc ? alpha * dalpha : 0.f;
+                // colour less what it hides, on g: dL/dalpha = T u
+                const float u = __fmaf_rn(s.b, g2[k], __fmaf_rn(s.g, g1[k], __fmaf_rn(s.r, g0[k], -A[k])));
+                A[k] = __fmaf_rn(alpha, u, A[k]);
+                // dL/dpower = alpha dL/dalpha below the cap; a capped entry passes nothing
+                const float dpow = oG < kAlphaMax ? w * u : 0.f;
                 const float pdy = dpow * dy;
                 p0 += dpow;
                 p1 += pdy;
                 p2 = __fmaf_rn(pdy, dy, p2);
             }
-            if (__ballot(any) == 0) continue;
-            // the lane's share of the nine accumulator entries; power = -(a dx^2
-            // + c dy^2)/2 - b dx dy with dx = px - mean_x, so dmean2d = (a m_x +
-            // b m_y, c m_y + b m_x) and dconic = -(m_xx / 2, m_xy, m_yy / 2)
-            const float m_x = dx * p0;
-            float v[kAccStride];
-            v[0] = __fmaf_rn(s.ca, m_x, s.cb * p1);
-            v[1] = __fmaf_rn(s.cc, p1, s.cb * m_x);
-            v[2] = -0.5f * dx * m_x;
-            v[3] = -dx * p1;
-            v[4] = -0.5f * p2;
-            v[5] = a_dop;
-            v[6] = a_c0;
-            v[7] = a_c1;
-            v[8] = a_c2;
-            // Row sums by butterfly: entries 0..7 halve per exchange (partner
-            // lane ^ 1, then ^ 2: each lane keeps half and adds the partner's
-            // copy of it), then the four lanes of a row with the same lane % 4
-            // are added (rotations by 4 and 8); entry 8 is summed plainly. Lane
-            // l < 8 of a row then holds entry bsel(l), lane 8 entry 8, and the
-            // four rows are added across.
-            float u[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float keep = b0 ? v[4 + i] : v[i], give = b0 ? v[i] : v[4 + i];
-                u[i] = keep + dpp_f32<0xB1>(give);
-            }
-            float w2[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float keep = b1 ? u[2 + i] : u[i], give = b1 ? u[i] : u[2 + i];
-                w2[i] = keep + dpp_f32<0x4E>(give);
-                w2[i] += dpp_f32<0x124>(w2[i]);
-                w2[i] += dpp_f32<0x128>(w2[i]);
-            }
-            // (the DPP row sum must run in every lane: a disabled source lane
-            // reads as zero, so it stays outside any condition)
-            const float s8 = row_sum(v[8]);
-            float t = b2 ? w2[1] : w2[0];
-            t = (row_lane & 8) ? s8 : t;
-            t += __shfl_xor(t, 16);
-            t += __shfl_xor(t, 32);
-            if (lane < kAccStride) atomicAdd(acc + (size_t)s.id * kAccStride + entry, t);
+            if (any == 0) continue;
+            const float t = wave_reduce9(p0, p1, p2, a_c0, a_c1, a_c2, dx, red_row, red_hi8, red_odd4, red_src);
+            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, j);
+            if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -628,22 +660,21 @@ __global__ __launch_bounds__(kWave) void k_blend_count(Cam cam, const gs_splat* 
 #pragma unroll
         for (int k = 0; k < kPix; ++k) walked[k] += T[k] > 0.f ? 1u : 0u;   // visited while blending
         const float4* rec = reinterpret_cast<const float4*>(splats + values[p]);
-        const float4 w0 = rec[0], w1 = rec[1], w2 = rec[2];
-        SplatReg s;
-        s.mx = w0.x; s.my = w0.y; s.ca = w0.z; s.cb = w0.w; s.cc = w1.x; s.op = w1.y;
-        s.pmin = w2.y; s.ex = w2.z; s.ey = w2.w;
-        if (!(fabsf(s.mx - box_cx) <= s.ex + box_hx && fabsf(s.my - box_cy) <= s.ey + box_hy)) continue;
+        const float4 c0 = rec[0], c1 = rec[1], c2 = rec[2];
+        if (!(fabsf(c0.x - box_cx) <= c2.z + box_hx && fabsf(c0.y - box_cy) <= c2.w + box_hy)) continue;
+        float4 w0, w1;
+        float2 w2;
+        stage_words(c0, c1, c2, w0, w1, w2);
+        const Staged s = staged(w0, w1, w2);
         const float dx = px - s.mx;
         const Quad q = column_quad(s, dx);
-        const float pmin2 = s.pmin * kLog2e;
 #pragma unroll
         for (int k = 0; k < kPix; ++k) {
             if (!(T[k] > 0.f)) continue;
             ++eval_fwd[k];
-            const float power2 = quad_power(q, py[k] - s.my);
-            if (!(power2 <= 0.f && power2 >= pmin2)) { ++pending[k]; continue; }
-            const float alpha = fminf(kAlphaMax, s.op * __builtin_amdgcn_exp2f(power2));
-            if (!(alpha >= kAlphaMin)) { ++pending[k]; continue; }
+            const float e = quad_neg_power(s, q, py[k] - s.my);
+            if (!in_reach(e, s.e_max)) { ++pending[k]; continue; }
+            const float alpha = fminf(kAlphaMax, s.op * __builtin_amdgcn_exp2f(-e));
             const float Tn = T[k] * (1.f - alpha);
             if (Tn < kTMin) { T[k] = -T[k]; continue; }
             T[k] = Tn;

@@ -49,8 +49,13 @@ constexpr int kSplatRectWord = 12;   // float offset of the packed rectangle
 static_assert(offsetof(gs_splat, rect) == 4 * kSplatRectWord, "rectangle offset");
 static_assert(offsetof(gs_splat, power_min) == 36 && offsetof(gs_splat, depth) == 56, "record layout");
 
-// Per-Gaussian screen-space gradient accumulator written by the blend backward.
-// Stride 9 floats: dmean_x, dmean_y, dconic_a, dconic_b, dconic_c, dopacity, dcolor rgb.
+// Per-Gaussian accumulator written by the blend backward, 9 floats: with dP =
+// dL/dpower of an uncapped pixel and (dx, dy) its centre minus the projected
+// mean, the sums over the pixels of dP, dP dx, dP dy, dP dx^2, dP dx dy,
+// dP dy^2, then dL/dcolour. Power = -(a dx^2 + c dy^2)/2 - b dx dy, so the
+// conic, mean and opacity gradients are linear in these sums with factors that
+// are the Gaussian's own (geometry_bwd): the preprocess backward
+// applies them once per Gaussian.
 constexpr int kAccStride = 9;
 
 // Radix-sort geometry: 256 threads x 16 keys per workgroup and digits of at
