@@ -1,5 +1,6 @@
 // Tile blend (Sec. 3.1) and its reverse. A 16x16 tile is covered by 4/PIX
-// independent wave64s (PIX = 2 in the forward, 4 in the backward); wave w owns
+// independent wave64s (PIX = 2 in the forward, 4 in the backward, fewer where an
+// image has few tiles); wave w owns
 // the 4 PIX contiguous rows from 4 PIX w, and every lane PIX pixels of one
 // column (rows 4k apart), so a lane's pixels share dx and the quadratic form
 // costs two fused multiply-adds per pixel. Each wave walks the tile's
@@ -24,15 +25,24 @@ namespace {
 
 constexpr int kXcds = 8;
 
-// Pixels per lane of the forward and the backward (1, 2 or 4). The forward's
-// two waves per tile halve the longest walks' time, which sets its end (its
-// tiles' walks differ by 3x and cannot be ordered before blending).
-#ifndef GS_FWD_PIX
-#define GS_FWD_PIX 2
-#endif
-#ifndef GS_BWD_PIX
-#define GS_BWD_PIX 4
-#endif
+// Pixels per lane (1, 2 or 4: four, two or one wave per tile), by the number of
+// tiles. Few tiles leave the SIMDs (1,024) short of waves, and the kernel lasts
+// as long as its longest walk: more waves per tile shorten each, at the price of
+// each splat's set-up and reduction once per wave. The lines lie where both
+// sides measure equal (us, 1 / 2 / 4 pixels per lane):
+//   backward:  64 tiles 75 / 118 / 197, 600 tiles 90 / 122 / 209,
+//              1200 tiles 90 / 105 / 170, 1900 tiles 130 / 127 / 175,
+//              2560 tiles 155 / 145 / 161, 3200 tiles 207 / 194 / 193
+//   forward:   64 tiles 43 / 75, 600 tiles 62 / 89, 1200 tiles 62 / 76,
+//              1900 tiles 87 / 90, 2560 tiles 91 / 92, 3200 tiles 121 / 115
+inline int fwd_pix(int n_tiles) { return n_tiles <= 2048 ? 1 : 2; }
+inline int bwd_pix(int n_tiles) { return n_tiles <= 1536 ? 1 : n_tiles <= 3072 ? 2 : 4; }
+
+// Splats per step of the walks with one pixel per lane: a wave nearly alone on
+// its SIMD waits for each splat's LDS reads and exponential, which a step's
+// splats share (64 tiles: forward 56 us with one, 52 with two, 43 with four,
+// backward 77, 75 and 76).
+constexpr int kFwdGroup = 4, kBwdGroup = 2;
 
 __device__ __forceinline__ int tile_of_block(int block, int n_tiles)
 {
@@ -273,34 +283,76 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_fwd(Cam cam, con
             c0 = p[0]; c1 = p[1]; c2 = p[2];
         }
         if (b + 2 * kWave + lane < end) nid = values[b + 2 * kWave + lane];
-        while (todo != 0) {
-            const int j = (int)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
-            const float dx = px - s.mx;
-            const Quad q = column_quad(s, dx);
-            alive = 0;
+        if constexpr (kPix == 1) {
+            // few tiles: a step takes kFwdGroup splats, whose reads and exponentials
+            // overlap, without branches; only the transmittance goes from one to
+            // the next (the same operations per pixel as below)
+            while (todo != 0) {
+                Staged s[kFwdGroup];
+                float alpha[kFwdGroup];
+                uint32_t pos[kFwdGroup];
+                uint64_t in[kFwdGroup];
+                int j = 0;
 #pragma unroll
-            for (int k = 0; k < kPix; ++k) {
-                // one branch per pixel; the stop rule is a select inside it
-                const float e = quad_neg_power(s, q, py[k] - s.my);
-                const bool on = T[k] > 0.f;
-                alive |= __ballot(on);
-                if (on & in_reach(e, s.e_max)) {
-                    const float alpha = fminf(kAlphaMax, s.op * __builtin_amdgcn_exp2f(-e));
-                    const float Tn = T[k] * (1.f - alpha);
-                    const bool stop = Tn < kTMin;
-                    const float w = stop ? 0.f : alpha * T[k];
-                    C0[k] = __fmaf_rn(s.r, w, C0[k]);
-                    C1[k] = __fmaf_rn(s.g, w, C1[k]);
-                    C2[k] = __fmaf_rn(s.b, w, C2[k]);
-                    last[k] = stop ? last[k] : b - start + (uint32_t)j + 1;
-                    T[k] = stop ? -T[k] : Tn;
+                for (int g = 0; g < kFwdGroup; ++g) {
+                    const uint64_t some = todo != 0 ? ~0ull : 0ull;   // none left: the last one again, masked out
+                    j = todo != 0 ? (int)__builtin_ctzll(todo) : j;
+                    todo &= todo - 1;
+                    s[g] = staged(st.w[0][j], st.w[1][j], st.tail(j));
+                    pos[g] = b - start + (uint32_t)j + 1;
+                    in[g] = some;
                 }
+#pragma unroll
+                for (int g = 0; g < kFwdGroup; ++g) {
+                    const float e = quad_neg_power(s[g], column_quad(s[g], px - s[g].mx), py[0] - s[g].my);
+                    in[g] &= __ballot(in_reach(e, s[g].e_max));
+                    alpha[g] = fminf(kAlphaMax, s[g].op * __builtin_amdgcn_exp2f(-e));
+                }
+#pragma unroll
+                for (int g = 0; g < kFwdGroup; ++g) {
+                    const bool on = __builtin_amdgcn_inverse_ballot_w64(in[g] & __ballot(T[0] > 0.f));
+                    const float Tn = T[0] * (1.f - alpha[g]);
+                    const bool stop = Tn < kTMin;
+                    const float w = stop ? 0.f : alpha[g] * T[0];
+                    C0[0] = on ? __fmaf_rn(s[g].r, w, C0[0]) : C0[0];
+                    C1[0] = on ? __fmaf_rn(s[g].g, w, C1[0]) : C1[0];
+                    C2[0] = on ? __fmaf_rn(s[g].b, w, C2[0]) : C2[0];
+                    last[0] = on && !stop ? pos[g] : last[0];
+                    T[0] = on ? (stop ? -T[0] : Tn) : T[0];
+                }
+                alive = __ballot(T[0] > 0.f);
+                if (alive == 0) break;
             }
-            // no pixel was still blending before this splat (found one visit late:
-            // the comparisons are those of the branches above)
-            if (alive == 0) break;
+        } else {
+            while (todo != 0) {
+                const int j = (int)__builtin_ctzll(todo);
+                todo &= todo - 1;
+                const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
+                const float dx = px - s.mx;
+                const Quad q = column_quad(s, dx);
+                alive = 0;
+#pragma unroll
+                for (int k = 0; k < kPix; ++k) {
+                    // one branch per pixel; the stop rule is a select inside it
+                    const float e = quad_neg_power(s, q, py[k] - s.my);
+                    const bool on = T[k] > 0.f;
+                    alive |= __ballot(on);
+                    if (on & in_reach(e, s.e_max)) {
+                        const float alpha = fminf(kAlphaMax, s.op * __builtin_amdgcn_exp2f(-e));
+                        const float Tn = T[k] * (1.f - alpha);
+                        const bool stop = Tn < kTMin;
+                        const float w = stop ? 0.f : alpha * T[k];
+                        C0[k] = __fmaf_rn(s.r, w, C0[k]);
+                        C1[k] = __fmaf_rn(s.g, w, C1[k]);
+                        C2[k] = __fmaf_rn(s.b, w, C2[k]);
+                        last[k] = stop ? last[k] : b - start + (uint32_t)j + 1;
+                        T[k] = stop ? -T[k] : Tn;
+                    }
+                }
+                // no pixel was still blending before this splat (found one visit late:
+                // the comparisons are those of the branches above)
+                if (alive == 0) break;
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -326,8 +378,12 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
                             hipStream_t s)
 {
     const int n_tiles = cam.tiles_x * cam.tiles_y;
-    hipLaunchKernelGGL(k_blend_fwd<GS_FWD_PIX>, dim3(blend_grid(n_tiles)), dim3(kTile * kTile / GS_FWD_PIX), 0, s,
-                       cam, splats, values, tile_ranges, image, final_T, n_contrib);
+    auto launch = [&](auto kernel, int pix) {
+        hipLaunchKernelGGL(kernel, dim3(blend_grid(n_tiles)), dim3(kTile * kTile / pix), 0, s, cam, splats, values,
+                           tile_ranges, image, final_T, n_contrib);
+    };
+    if (fwd_pix(n_tiles) == 1) launch(k_blend_fwd<1>, 1);
+    else launch(k_blend_fwd<2>, 2);
     return hipGetLastError();
 }
 
@@ -448,50 +504,109 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
             c0 = r[0]; c1 = r[1]; c2 = r[2];
             if (bi > 1) nid = values[start + b - 2 * kWave + lane];
         }
-        while (todo != 0) {
-            const int j = 63 - (int)__builtin_clzll(todo);
-            todo ^= 1ull << j;
-            const uint32_t pos = b + (uint32_t)j;
-            const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
-            const float dx = px - s.mx;
-            const Quad q = column_quad(s, dx);
-            // per-lane sums over its pixels: colour gradient and dL/dpower times
-            // 1, dy, dy^2 (the lane's pixels share dx)
-            float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f;
-            float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-            uint64_t any = 0;
+        if constexpr (kPix == 1) {
+            // few tiles: kBwdGroup splats a step, without branches, as in the forward;
+            // the transmittance and the colour behind go from one to the next. A
+            // lane that a splat does not reach takes its values by selects (a
+            // product with zero would pass on an infinite colour or gradient).
+            while (todo != 0) {
+                Staged s[kBwdGroup];
+                float dx[kBwdGroup], dy[kBwdGroup], oG[kBwdGroup], alpha[kBwdGroup], inv[kBwdGroup];
+                uint64_t in[kBwdGroup];
+                int js[kBwdGroup];
+                int j = 0;
 #pragma unroll
-            for (int k = 0; k < kPix; ++k) {
-                // one branch per pixel (no short circuit); the cap is a select inside it
-                const float dy = py[k] - s.my;
-                const float e = quad_neg_power(s, q, dy);
-                // the comparisons' lane masks, combined as scalars
-                const uint64_t reach = __ballot(pos < last[k]) & __ballot(in_reach(e, s.e_max));
-                any |= reach;
-                if (!__builtin_amdgcn_inverse_ballot_w64(reach)) continue;
-                const float oG = s.op * __builtin_amdgcn_exp2f(-e);
-                const float alpha = fminf(kAlphaMax, oG);
-                // hardware reciprocal (1 ulp): T is recovered over a few hundred
-                // splats, so its relative error stays near 1e-5
-                T[k] *= __builtin_amdgcn_rcpf(1.f - alpha);   // transmittance in front of this splat
-                const float w = alpha * T[k];
-                a_c0 = __fmaf_rn(w, g0[k], a_c0);
-                a_c1 = __fmaf_rn(w, g1[k], a_c1);
-                a_c2 = __fmaf_rn(w, g2[k], a_c2);
-                // colour less what it hides, on g: dL/dalpha = T u
-                const float u = __fmaf_rn(s.b, g2[k], __fmaf_rn(s.g, g1[k], __fmaf_rn(s.r, g0[k], -A[k])));
-                A[k] = __fmaf_rn(alpha, u, A[k]);
-                // dL/dpower = alpha dL/dalpha below the cap; a capped entry passes nothing
-                const float dpow = oG < kAlphaMax ? w * u : 0.f;
-                const float pdy = dpow * dy;
-                p0 += dpow;
-                p1 += pdy;
-                p2 = __fmaf_rn(pdy, dy, p2);
+                for (int g = 0; g < kBwdGroup; ++g) {
+                    const uint64_t some = todo != 0 ? ~0ull : 0ull;   // none left: the last one again, masked out
+                    j = todo != 0 ? 63 - (int)__builtin_clzll(todo) : j;
+                    todo &= ~(1ull << j);
+                    s[g] = staged(st.w[0][j], st.w[1][j], st.tail(j));
+                    js[g] = j;
+                    in[g] = some;
+                }
+#pragma unroll
+                for (int g = 0; g < kBwdGroup; ++g) {
+                    dx[g] = px - s[g].mx;
+                    dy[g] = py[0] - s[g].my;
+                    const float e = quad_neg_power(s[g], column_quad(s[g], dx[g]), dy[g]);
+                    in[g] &= __ballot(b + (uint32_t)js[g] < last[0]) & __ballot(in_reach(e, s[g].e_max));
+                    oG[g] = s[g].op * __builtin_amdgcn_exp2f(-e);
+                    alpha[g] = __builtin_amdgcn_inverse_ballot_w64(in[g]) ? fminf(kAlphaMax, oG[g]) : 0.f;
+                    inv[g] = __builtin_amdgcn_rcpf(1.f - alpha[g]);
+                }
+                float p0[kBwdGroup], p1[kBwdGroup], p2[kBwdGroup], ac0[kBwdGroup], ac1[kBwdGroup], ac2[kBwdGroup];
+#pragma unroll
+                for (int g = 0; g < kBwdGroup; ++g) {
+                    const bool on = __builtin_amdgcn_inverse_ballot_w64(in[g]);
+                    T[0] *= inv[g];
+                    const float w = alpha[g] * T[0];
+                    ac0[g] = on ? w * g0[0] : 0.f;
+                    ac1[g] = on ? w * g1[0] : 0.f;
+                    ac2[g] = on ? w * g2[0] : 0.f;
+                    const float u = __fmaf_rn(s[g].b, g2[0], __fmaf_rn(s[g].g, g1[0], __fmaf_rn(s[g].r, g0[0], -A[0])));
+                    A[0] = on ? __fmaf_rn(alpha[g], u, A[0]) : A[0];
+                    p0[g] = on && oG[g] < kAlphaMax ? w * u : 0.f;
+                    p1[g] = p0[g] * dy[g];
+                    p2[g] = p1[g] * dy[g];
+                }
+                float t[kBwdGroup];
+#pragma unroll
+                for (int g = 0; g < kBwdGroup; ++g)
+                    t[g] = wave_reduce9(p0[g], p1[g], p2[g], ac0[g], ac1[g], ac2[g], dx[g], red_row, red_hi8, red_odd4,
+                                        red_src);
+#pragma unroll
+                for (int g = 0; g < kBwdGroup; ++g) {
+                    if (in[g] == 0) continue;
+                    const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, js[g]);
+                    if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t[g]);
+                }
             }
-            if (any == 0) continue;
-            const float t = wave_reduce9(p0, p1, p2, a_c0, a_c1, a_c2, dx, red_row, red_hi8, red_odd4, red_src);
-            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, j);
-            if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t);
+        } else {
+            while (todo != 0) {
+                const int j = 63 - (int)__builtin_clzll(todo);
+                todo ^= 1ull << j;
+                const uint32_t pos = b + (uint32_t)j;
+                const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
+                const float dx = px - s.mx;
+                const Quad q = column_quad(s, dx);
+                // per-lane sums over its pixels: colour gradient and dL/dpower times
+                // 1, dy, dy^2 (the lane's pixels share dx)
+                float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f;
+                float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+                uint64_t any = 0;
+#pragma unroll
+                for (int k = 0; k < kPix; ++k) {
+                    // one branch per pixel (no short circuit); the cap is a select inside it
+                    const float dy = py[k] - s.my;
+                    const float e = quad_neg_power(s, q, dy);
+                    // the comparisons' lane masks, combined as scalars
+                    const uint64_t reach = __ballot(pos < last[k]) & __ballot(in_reach(e, s.e_max));
+                    any |= reach;
+                    if (!__builtin_amdgcn_inverse_ballot_w64(reach)) continue;
+                    const float oG = s.op * __builtin_amdgcn_exp2f(-e);
+                    const float alpha = fminf(kAlphaMax, oG);
+                    // hardware reciprocal (1 ulp): T is recovered over a few hundred
+                    // splats, so its relative error stays near 1e-5
+                    T[k] *= __builtin_amdgcn_rcpf(1.f - alpha);   // transmittance in front of this splat
+                    const float w = alpha * T[k];
+                    a_c0 = __fmaf_rn(w, g0[k], a_c0);
+                    a_c1 = __fmaf_rn(w, g1[k], a_c1);
+                    a_c2 = __fmaf_rn(w, g2[k], a_c2);
+                    // colour less what it hides, on g: dL/dalpha = T u
+                    const float u = __fmaf_rn(s.b, g2[k], __fmaf_rn(s.g, g1[k], __fmaf_rn(s.r, g0[k], -A[k])));
+                    A[k] = __fmaf_rn(alpha, u, A[k]);
+                    // dL/dpower = alpha dL/dalpha below the cap; a capped entry passes nothing
+                    const float dpow = oG < kAlphaMax ? w * u : 0.f;
+                    const float pdy = dpow * dy;
+                    p0 += dpow;
+                    p1 += pdy;
+                    p2 = __fmaf_rn(pdy, dy, p2);
+                }
+                if (any == 0) continue;
+                const float t = wave_reduce9(p0, p1, p2, a_c0, a_c1, a_c2, dx, red_row, red_hi8, red_odd4, red_src);
+                const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, j);
+                if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t);
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -504,9 +619,15 @@ hipError_t launch_blend_bwd(const Cam& cam, const gs_splat* splats, const uint32
                             const float* dL_dimage, const uint32_t* tile_order, float* acc, hipStream_t s)
 {
     const int n_tiles = cam.tiles_x * cam.tiles_y;
-    hipLaunchKernelGGL(k_blend_bwd<GS_BWD_PIX>, dim3(tile_order ? n_tiles : blend_grid(n_tiles)),
-                       dim3(kTile * kTile / GS_BWD_PIX), 0, s, cam, splats, values, tile_ranges, final_T, n_contrib,
-                       dL_dimage, tile_order, acc);
+    auto launch = [&](auto kernel, int pix) {
+        hipLaunchKernelGGL(kernel, dim3(tile_order ? n_tiles : blend_grid(n_tiles)), dim3(kTile * kTile / pix), 0, s,
+                           cam, splats, values, tile_ranges, final_T, n_contrib, dL_dimage, tile_order, acc);
+    };
+    switch (bwd_pix(n_tiles)) {
+    case 1: launch(k_blend_bwd<1>, 1); break;
+    case 2: launch(k_blend_bwd<2>, 2); break;
+    default: launch(k_blend_bwd<4>, 4); break;
+    }
     return hipGetLastError();
 }
 

@@ -104,6 +104,19 @@ def test_backward_tile_order_limit(tiles_x):
     check_all(sc, tiny_camera(16 * tiles_x, 256), label="wide-bwd-%d" % tiles_x)
 
 
+@pytest.mark.parametrize("tiles", [(48, 32), (29, 53), (64, 32), (3, 683), (64, 48), (7, 439)])
+def test_pixels_per_lane_limits(tiles):
+    # 1536, 2048 and 3072 tiles and the next sizes above them, where the blend
+    # kernels take more pixels per lane: clustered splats (long lists, a count
+    # that is no multiple of the splats per step, saturated pixels) and a
+    # background that stays in sight
+    w, h = 16 * tiles[0] - 5, 16 * tiles[1] - 3
+    sc = inputs.make_scene("medium", n=3001)
+    sc.log_scales += np.float32(0.8)
+    sc.opacity_logits += np.float32(1.5)
+    check_all(sc, tiny_camera(w, h, bg=(0.2, 0.4, 0.1)), label="pix-%dx%d" % tiles)
+
+
 @pytest.mark.parametrize("degree", [3, 1])
 def test_sh3_backward_without_the_colour_jacobian(degree):
     # gs_preprocessed.color_jac NULL: the preprocess writes no view-direction
