@@ -52,7 +52,6 @@ __device__ __forceinline__ int tile_of_block(int block, int n_tiles)
 
 inline int blend_grid(int n_tiles) { return (int)div_up(n_tiles, kXcds) * kXcds; }
 
-constexpr float kPowerMargin = 1e-3f;   // of gs_splat.power_min below -ln(255 opacity)
 constexpr float kAlphaMax = 0.99f;
 constexpr float kTMin = 0.0001f;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -62,7 +61,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // quadratic form taken once by the lane that stages it. In base-2 units (times
 // log2 e), so that exp(power) is one hardware exp2: -power log2 e = ka dx^2 +
 // kb dx dy + kc dy^2. e_max is its bound where alpha reaches 1/255,
-// log2(255 opacity), from power_min less its margin.
+// log2(255 opacity).
 struct Staged {
     float mx, my, ka, kb, kc, op, r, g, b, e_max;
 };
@@ -72,7 +71,12 @@ __device__ __forceinline__ void stage_words(const float4& c0, const float4& c1, 
 {
     w0 = make_float4(c0.x, c0.y, (0.5f * kLog2e) * c0.z, kLog2e * c0.w);
     w1 = make_float4((0.5f * kLog2e) * c1.x, c1.y, c1.z, c1.w);
-    const float reach = -kLog2e * (c2.y + kPowerMargin);
+    // the hardware logarithm corrected by the residual of its exponential: within
+    // half an ulp and a few 1e-8, so that the alpha test decides as closely on the
+    // logarithms as o e^power >= 1/255 does
+    const float r255 = 255.f * c1.y;
+    const float l = __builtin_amdgcn_logf(r255);
+    const float reach = __fmaf_rn(__fmaf_rn(r255, __builtin_amdgcn_exp2f(-l), -1.f), kLog2e, l);
     w2 = make_float2(c2.x, reach > 0.f ? reach : 0.f);
 }
 
