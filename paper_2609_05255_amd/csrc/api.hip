@@ -219,15 +219,17 @@ Workspace layout_workspace(void* base, int64_t n, uint64_t capacity, int32_t kin
     w.block_pairs = (uint32_t*)take(sizeof(uint32_t) * pair_count_slots(nn));
     w.keys_a = (uint32_t*)take(sizeof(uint32_t) * nn);
     w.keys_b = (uint32_t*)take(sizeof(uint32_t) * nn);
-    w.vals_a = (uint32_t*)take(sizeof(uint32_t) * nn);
-    w.vals_b = (uint32_t*)take(sizeof(uint32_t) * nn);
+    w.vals_a = (uint2*)take(sizeof(uint2) * nn);
+    w.vals_b = (uint2*)take(sizeof(uint2) * nn);
     // the depth sort's 8-bit digits over n keys; the block sort's up to 9-bit
     // digits over up to `capacity` entries
-    w.hist = (uint32_t*)take(sizeof(uint32_t) * std::max(kRadix * div_up(nn, kSortTile),
-                                                         2 * kRadix * div_up(cap, kBlock * kBlockSortItems)));
-    w.digit_tot = (uint32_t*)take(sizeof(uint32_t) * kRadix * 4);
+    w.hist = (uint32_t*)take(sizeof(uint32_t) * std::max(kRadix * div_up(nn, kDepthSortTile),
+                                                         2 * kRadix * div_up(cap, kBlockSortTile)));
+    const int64_t dsup = (int64_t)4 * radix_groups(nn, kDepthSortTile) * kRadix;
+    w.sup_count = dsup + (int64_t)2 * radix_groups(cap, kBlockSortTile) * 2 * kRadix;
+    w.depth_sup = (uint32_t*)take(sizeof(uint32_t) * w.sup_count);
+    w.block_sup = w.depth_sup ? w.depth_sup + dsup : nullptr;
     w.scan_part = (uint32_t*)take(sizeof(uint32_t) * (div_up(nn, kDupChunk) + 1));
-    w.sorted_rect = (uint2*)take(sizeof(uint2) * nn);
     w.entry_count = (uint64_t*)take(sizeof(uint64_t));
     w.entry_keys_a = (uint32_t*)take(sizeof(uint32_t) * cap);
     w.entry_vals_a = (uint32_t*)take(sizeof(uint32_t) * cap);
@@ -440,16 +442,16 @@ gs_status gs_bin_sort(const gs_camera* cam, const gs_preprocessed* pre, int64_t 
     // block entries: at most one per pair, counted on the device (the grids
     // are sized for the capacity in both modes)
     const PairCount entries{ws.entry_count, capacity, capacity};
-    const uint32_t* order = nullptr;
+    DepthOrder order{nullptr, nullptr, nullptr};
     BlockEntries ent{nullptr, nullptr};
     timing_begin(GS_KERNEL_DEPTH_SORT, s);
-    GS_HIP(launch_depth_sort(n, pre->depth_key, pre->splats, ws, &order, s));
+    GS_HIP(launch_depth_sort(c, n, pre->depth_key, pre->splats, ws, &order, s));
     timing_end(GS_KERNEL_DEPTH_SORT, s);
     timing_begin(GS_KERNEL_ENTRY_OFFSETS, s);
-    GS_HIP(launch_entry_offsets(n, pairs, ws, s));
+    GS_HIP(launch_entry_offsets(n, pairs, order, ws, s));
     timing_end(GS_KERNEL_ENTRY_OFFSETS, s);
     timing_begin(GS_KERNEL_BLOCK_ENTRIES, s);
-    GS_HIP(launch_block_entries(c, n, order, entries, ws, s));
+    GS_HIP(launch_block_entries(c, n, order, pairs, capacity, ws, s));
     timing_end(GS_KERNEL_BLOCK_ENTRIES, s);
     timing_begin(GS_KERNEL_BLOCK_SORT, s);
     GS_HIP(launch_block_sort(c, entries, ws, &ent, s));

@@ -58,12 +58,12 @@ static_assert(offsetof(gs_splat, power_min) == 36 && offsetof(gs_splat, depth) =
 // applies them once per Gaussian.
 constexpr int kAccStride = 9;
 
-// Radix-sort geometry: 256 threads x 16 keys per workgroup and digits of at
-// most 8 bits for the depth sort (n keys); x 32 keys and 9 bits for the block
-// sort (the entries).
-constexpr int kSortItems = 16;
-constexpr int kBlockSortItems = 32;
-constexpr int kSortTile = kBlock * kSortItems;   // 4096
+// Radix-sort geometry: workgroups of 1,024 threads, 4 to 12 keys per thread and
+// 8-bit digits for the depth sort (n keys), 8 or 16 and up to 9 bits for the
+// block sort (the entries).
+constexpr int kBlockSortItems = 8;
+constexpr int kBlockSortTile = 1024 * kBlockSortItems;   // the fewest keys per workgroup
+constexpr int kDepthSortTile = 1024 * 4;   // the fewest keys per workgroup
 constexpr int kRadix = 256;
 constexpr int kDupChunk = 1024;   // depth-ordered Gaussians per workgroup in entry emission
 constexpr int kBlockDim = 4;      // a block is kBlockDim x kBlockDim tiles
@@ -87,12 +87,13 @@ struct Workspace {
     uint32_t* block_pairs;   // [pair_count_slots] tile sums per preprocess workgroup or wave
     uint32_t* keys_a;        // [n]               depth-sort ping-pong keys
     uint32_t* keys_b;        // [n]
-    uint32_t* vals_a;        // [n]               depth-sort values
-    uint32_t* vals_b;        // [n]
-    uint32_t* hist;          // [digits][workgroups] of a radix pass (256 x n / 4096, 512 x capacity / 8192)
-    uint32_t* digit_tot;     // [4 passes][256]   digit totals of each pass
+    uint2* vals_a;           // [n]               depth-sort values: index and packed tile rectangle (large grids:
+    uint2* vals_b;           // [n]               indices in vals_a, rectangles gathered in depth order in vals_b)
+    uint32_t* hist;          // [workgroups][digits] of a radix pass (up to n / 4096 x 256, capacity / 8192 x 512)
+    uint32_t* depth_sup;     // [4][groups][256]  group sums of the depth sort's passes
+    uint32_t* block_sup;     // [2][groups][512]  and of the block sort's, right behind them
+    int64_t sup_count;       // values of both
     uint32_t* scan_part;     // [n / kDupChunk + 1] chunk sums of the entry-offset scan
-    uint2* sorted_rect;      // [n]               tile rectangles in depth order (empty for culled)
     uint64_t* entry_count;   // [1]               block entries (0 when the pairs exceed the capacity)
     uint32_t* entry_keys_a;  // [capacity]        entry keys: block id << 16 | tile mask
     uint32_t* entry_vals_a;  // [capacity]        entry values: Gaussian index
@@ -136,15 +137,25 @@ struct PairCount {
 hipError_t launch_preprocess(const Cam& cam, const gs_gaussians& g, const gs_appearance& app,
                              const gs_preprocessed& out, const Workspace& ws, int* slots, hipStream_t s);
 hipError_t launch_pair_count(int slots, const Workspace& ws, uint64_t* num_pairs, hipStream_t s);
-hipError_t launch_depth_sort(int64_t n, const uint32_t* depth_key, const gs_splat* splats, const Workspace& ws,
-                             const uint32_t** order_out, hipStream_t s);
-hipError_t launch_entry_offsets(int64_t n, PairCount pairs, const Workspace& ws, hipStream_t s);
+// The Gaussians in depth order: index and packed tile rectangle, or on large
+// grids (packed is NULL) indices and rectangles (empty for culled ones).
+struct DepthOrder {
+    const uint2* packed;
+    const uint32_t* gid;
+    const uint2* rect;
+};
+int radix_group(int nblocks);                  // workgroups per group sum of a radix pass
+int radix_groups(int64_t keys, int tile);      // group sums of a pass over that many keys
+hipError_t launch_depth_sort(const Cam& cam, int64_t n, const uint32_t* depth_key, const gs_splat* splats,
+                             const Workspace& ws, DepthOrder* out, hipStream_t s);
+hipError_t launch_entry_offsets(int64_t n, PairCount pairs, const DepthOrder& order, const Workspace& ws,
+                                hipStream_t s);
 int blocks_x_of(const Cam& cam);
 int blocks_y_of(const Cam& cam);
 int64_t segment_bound(const Cam& cam, uint64_t capacity);   // segments the tile-list kernels can meet
 bool blocks_supported(const Cam& cam);   // at most 65536 blocks: the block id shares a u32 key with a tile mask
-hipError_t launch_block_entries(const Cam& cam, int64_t n, const uint32_t* order, PairCount entries,
-                                const Workspace& ws, hipStream_t s);
+hipError_t launch_block_entries(const Cam& cam, int64_t n, const DepthOrder& order, PairCount pairs,
+                                uint64_t capacity, const Workspace& ws, hipStream_t s);
 struct BlockEntries {
     const uint32_t* key;   // block id << 16 | mask of the block's tiles the Gaussian meets
     const uint32_t* gid;   // Gaussian index

@@ -10,14 +10,14 @@
 // block's 16 tile lists are cut out of its entries by ordered (ballot)
 // compaction, each list written once, at its final place.
 //
-// One radix pass = k_radix_hist (per-workgroup digit counts) + k_radix_scan
-// (exclusive offsets per digit over workgroups) + k_radix_scatter: each wave
-// ranks a contiguous slice of the workgroup's keys with ballot-matched digits
-// (no workgroup barrier per round), the workgroup reorders its 4096 keys by
-// digit in LDS, and writes each digit's run to consecutive global addresses.
-// The grids are sized for the most keys a call can meet (the capacity, for
-// the block entries); workgroups past the device-side count do nothing, and
-// the scan reads only the workgroups below it. A single-pass block sort's
+// One radix pass = k_radix_hist (per-workgroup digit counts and their sums over
+// groups of workgroups) + k_radix_scatter: each workgroup adds up the counts
+// before its own, each wave ranks a contiguous slice of the workgroup's keys
+// with ballot-matched digits (no workgroup barrier per round), the workgroup
+// reorders its 4096 to 16384 keys by digit in LDS, and writes each digit's run to
+// consecutive global addresses. The grids are sized for the most keys a call can
+// meet (the capacity, for the block entries); workgroups past the device-side
+// count do nothing, and their rows are not read. A single-pass block sort's
 // scatter has one workgroup more, which writes the tile lists' segment table
 // from that pass's digit totals (the blocks' entry counts).
 #include "gs_internal.h"
@@ -54,6 +54,33 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds4, 
     return before + x - v;
 }
 
+constexpr int kListThreads = 1024;   // radix passes, single-workgroup scans
+
+// Exclusive scan of one value per thread over a 1024-thread workgroup.
+template <typename T>
+__device__ __forceinline__ T wg_excl_scan_1024(T v, T* lds16, T* total)
+{
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    T x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) lds16[wave] = x;
+    __syncthreads();
+    T before = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kListThreads / kWave; ++w) {
+        const T s = lds16[w];
+        if (w < wave) before += s;
+        tot += s;
+    }
+    __syncthreads();
+    *total = tot;
+    return before + x - v;
+}
+
 // Lanes of this wave holding the same kBits-bit digit (restricted to valid lanes).
 template <int kBits>
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
@@ -72,64 +99,84 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
     return ((uint64_t)hi << 32) | lo;
 }
 
-template <int kBits, int kItems, typename KeyT>
-__global__ __launch_bounds__(kBlock) void k_radix_hist(const KeyT* __restrict__ keys, PairCount cnt, int shift,
-                                                       uint32_t* __restrict__ hist, int nblocks)
+// Digit counts of each workgroup's keys, one row of R counts per workgroup, and
+// their sums over groups of `group` workgroups (sup, zeroed beforehand), from
+// which the scatter takes its digits' positions: about sqrt(workgroups) rows of
+// either kind. A kernel of its own that scanned each digit's counts over the
+// workgroups took 5 us and a launch per pass at any size; adding the rows up in
+// the scatter costs about 1 us of it.
+template <int kBits, int kItems>
+__global__ __launch_bounds__(kListThreads) void k_radix_hist(const uint32_t* __restrict__ keys, PairCount cnt, int shift,
+                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ sup,
+                                                       int group)
 {
     constexpr int R = 1 << kBits;
-    constexpr int kTile = kBlock * kItems;
+    constexpr int kTile = kListThreads * kItems;
     const uint64_t count = cnt.get();
-    if ((uint64_t)blockIdx.x * kTile >= count) return;   // past the keys: the scan does not read it
-    // 16 copies of the counts (per wave and lane % 4): a skewed digit, such as
-    // the exponent byte of the depth keys, then meets at most 16 lanes of an
+    if ((uint64_t)blockIdx.x * kTile >= count) return;   // past the keys: the scatter does not read it
+    // 16 copies of the counts (per wave % 4 and lane % 4): a skewed digit, such
+    // as the exponent byte of the depth keys, then meets at most 16 lanes of an
     // instruction on one counter
     __shared__ uint32_t h[16][R];
-    for (int k = threadIdx.x; k < 16 * R; k += kBlock) (&h[0][0])[k] = 0;
+    for (int k = threadIdx.x; k < 16 * R; k += kListThreads) (&h[0][0])[k] = 0;
     __syncthreads();
-    const int copy = (threadIdx.x >> 6) * 4 + (threadIdx.x & 3);
+    const int copy = ((threadIdx.x >> 6) & 3) * 4 + (threadIdx.x & 3);
     const uint64_t base = (uint64_t)blockIdx.x * kTile;
     // all loads first (one memory round trip), then the counts
     uint32_t k[kItems];
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
-        const uint64_t idx = base + (uint64_t)r * kBlock + threadIdx.x;
-        k[r] = idx < count ? (uint32_t)keys[idx] : 0u;
+        const uint64_t idx = base + (uint64_t)r * kListThreads + threadIdx.x;
+        k[r] = idx < count ? keys[idx] : 0u;
     }
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
-        const uint64_t idx = base + (uint64_t)r * kBlock + threadIdx.x;
+        const uint64_t idx = base + (uint64_t)r * kListThreads + threadIdx.x;
         if (idx < count) atomicAdd(&h[copy][(k[r] >> shift) & (R - 1)], 1u);
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < R; d += kBlock) {
+    for (int d = threadIdx.x; d < R; d += kListThreads) {
         uint32_t c = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) c += h[w][d];
-        hist[(size_t)d * nblocks + blockIdx.x] = c;
+        hist[(size_t)blockIdx.x * R + d] = c;
+        if (c) atomicAdd(&sup[(size_t)(blockIdx.x / (unsigned)group) * R + d], c);
     }
 }
 
-// One workgroup per digit: exclusive scan of that digit's counts over the
-// workgroups that hold keys (the first ceil(count / tile) of the nblocks).
-__global__ __launch_bounds__(kBlock) void k_radix_scan(uint32_t* __restrict__ hist, int nblocks, PairCount cnt,
-                                                       int tile, uint32_t* __restrict__ digit_tot)
+// Column sums of every step-th row from r0 below r1 of a table of R-wide rows,
+// by one wave, into out[R]: its lanes take 16 bytes of a row each, several rows
+// in flight together.
+template <int R>
+__device__ __forceinline__ void sum_rows(const uint32_t* __restrict__ rows, int r0, int r1, int step, uint32_t* out)
 {
-    __shared__ uint32_t lds4[4];
-    uint32_t* row = hist + (size_t)blockIdx.x * nblocks;
-    const int active = (int)min((uint64_t)nblocks, (cnt.get() + (uint64_t)tile - 1) / (uint64_t)tile);
-    const int per = (active + kBlock - 1) / kBlock;
-    const int start = threadIdx.x * per;
-    const int end = min(start + per, active);
-    uint32_t sum = 0;
-    for (int k = start; k < end; ++k) sum += row[k];
-    uint32_t total;
-    uint32_t run = block_excl_scan(sum, lds4, &total);
-    for (int k = start; k < end; ++k) {
-        const uint32_t v = row[k];
-        row[k] = run;
-        run += v;
+    constexpr int kVec = R >= 4 ? 4 : R;                      // columns per load
+    constexpr int kCols = R / kVec;                           // loads per row
+    constexpr int kPer = kCols > kWave ? kCols / kWave : 1;   // loads per lane and row
+    constexpr int kFly = 4;                                   // rows in flight
+    const int lane = __lane_id();
+    if (lane >= kCols) return;
+    uint32_t sum[kPer][kVec] = {};
+    for (int r = r0; r < r1; r += step * kFly) {
+        uint32_t v[kFly][kPer][kVec];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u)
+#pragma unroll
+            for (int q = 0; q < kPer; ++q)
+#pragma unroll
+                for (int j = 0; j < kVec; ++j)
+                    v[u][q][j] = r + u * step < r1 ? rows[(size_t)(r + u * step) * R + (q * kWave + lane) * kVec + j] : 0u;
+#pragma unroll
+        for (int u = 0; u < kFly; ++u)
+#pragma unroll
+            for (int q = 0; q < kPer; ++q)
+#pragma unroll
+                for (int j = 0; j < kVec; ++j) sum[q][j] += v[u][q][j];
     }
-    if (threadIdx.x == 0) digit_tot[blockIdx.x] = total;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+#pragma unroll
+        for (int j = 0; j < kVec; ++j) out[(q * kWave + lane) * kVec + j] = sum[q][j];
 }
 
 // The block entries' segment table (see k_segments), written by one extra
@@ -142,65 +189,139 @@ struct SegTable {
     int n_blocks;
 };
 
-__device__ void segment_table_256(const uint32_t* __restrict__ block_count, const SegTable& t);
+__device__ void segment_table(const uint32_t* block_count, const SegTable& t);
 
-template <int kBits, int kItems, typename KeyT, typename KeyOutT>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT* __restrict__ keys_in,
-                                                          const uint32_t* __restrict__ vals_in, PairCount cnt,
-                                                          int shift, const uint32_t* __restrict__ hist, int nblocks,
-                                                          const uint32_t* __restrict__ digit_tot,
-                                                          KeyOutT* __restrict__ keys_out,
-                                                          uint32_t* __restrict__ vals_out,
-                                                          const gs_splat* __restrict__ rect_src,
+// A tile rectangle (x0 | y0 << 16, x1 | y1 << 16, half-open, not empty) of a
+// grid of at most 256 x 256 tiles in 32 bits: x0, y0, x1 - 1, y1 - 1. The
+// empty rectangle of a culled Gaussian has x0 above x1 - 1.
+constexpr uint32_t kEmptyRect32 = 0x0000FFFFu;
+
+__device__ __forceinline__ uint32_t pack_rect32(uint2 r)
+{
+    return (r.x & 0xFFu) | ((r.x >> 8) & 0xFF00u) | (((r.y & 0xFFFFu) - 1u) << 16) | (((r.y >> 16) - 1u) << 24);
+}
+
+__device__ __forceinline__ uint2 unpack_rect32(uint32_t p)
+{
+    if (p == kEmptyRect32) return make_uint2(0u, 0u);
+    return make_uint2((p & 0xFFu) | ((p << 8) & 0xFF0000u), (((p >> 16) & 0xFFu) + 1u) | (((p >> 24) + 1u) << 16));
+}
+
+// The values a pass moves: the Gaussian's index alone, or with it its packed
+// tile rectangle (x: index, y: rectangle).
+__device__ __forceinline__ uint32_t value_index(uint32_t v) { return v; }
+__device__ __forceinline__ uint32_t value_index(uint2 v) { return v.x; }
+
+// What a scatter pass does beside moving keys and values.
+enum PassMode {
+    kPlain,
+    kFirst,    // first depth pass: makes the values, (index, packed rectangle read from the record in index order)
+    kGather,   // last depth pass of a grid beyond 256 tiles a side: gathers the rectangles into depth order
+};
+
+__device__ __forceinline__ uint2 splat_rect(const gs_splat* __restrict__ splats, uint32_t i)
+{
+    return *reinterpret_cast<const uint2*>(reinterpret_cast<const uint32_t*>(splats + i) + kSplatRectWord);
+}
+
+// keys_out == nullptr drops the keys; vals_in == nullptr means value = position.
+template <int kBits, int kItems, typename ValT, int kMode>
+__global__ __launch_bounds__(kListThreads) void k_radix_scatter(const uint32_t* __restrict__ keys_in,
+                                                          const ValT* __restrict__ vals_in, PairCount cnt, int shift,
+                                                          const uint32_t* __restrict__ hist,
+                                                          const uint32_t* __restrict__ sup, int group,
+                                                          uint32_t* __restrict__ keys_out, ValT* __restrict__ vals_out,
+                                                          const gs_splat* __restrict__ splats,
                                                           uint2* __restrict__ rect_out, SegTable seg)
 {
     constexpr int R = 1 << kBits;
-    constexpr int kTile = kBlock * kItems;
-    constexpr int kSlice = kTile / (kBlock / kWave);   // keys per wave
-    __shared__ uint32_t wcnt[4][R];      // per-wave digit counts, then per-wave exclusive offsets
-    __shared__ uint32_t gbase[R];        // global position of this workgroup's first key of each digit
-    __shared__ uint32_t lstart[R];       // start of each digit in the workgroup's reordered keys
-    __shared__ KeyT skey[kTile];
-    __shared__ uint32_t sval[kTile];
-    __shared__ uint32_t lds4[4];
-    if (seg.block_ranges && blockIdx.x == gridDim.x - 1) {   // the extra workgroup
-        segment_table_256(digit_tot, seg);
-        return;
-    }
+    constexpr int kTile = kListThreads * kItems;
+    constexpr int kWaves = kListThreads / kWave;
+    constexpr int kSlice = kTile / kWaves;   // keys per wave
+    __shared__ uint32_t wcnt[kWaves][R];      // per-wave digit counts, then each wave's first place of each digit
+    __shared__ uint32_t gbase[R];        // global position of a digit's first key, less its place in the workgroup
+    __shared__ ValT buf[kTile];          // row sums, then the workgroup's keys, then its values, in digit order
+    __shared__ uint32_t lds16[kWaves];
+    static_assert(sizeof(buf) >= kWaves * R * sizeof(uint32_t), "row sums");
+    uint32_t (*part)[R] = reinterpret_cast<uint32_t (*)[R]>(buf);
+    uint32_t* kbuf = reinterpret_cast<uint32_t*>(buf);
     const uint64_t count = cnt.get();
-    if ((uint64_t)blockIdx.x * kTile >= count) return;   // past the keys: nothing to move
     const int t = threadIdx.x, wave = t >> 6, lane = __lane_id();
     // digits t * kDPT + j (consecutive per thread)
-    constexpr int kDPT = R > kBlock ? R / kBlock : 1;
-    uint32_t dtv[kDPT], dsum = 0;
-#pragma unroll
-    for (int j = 0; j < kDPT; ++j) {
-        const int d = t * kDPT + j;
-        dtv[j] = d < R ? digit_tot[d] : 0u;
-        dsum += dtv[j];
-    }
-    uint32_t dbase = block_excl_scan(dsum, lds4, nullptr);
-#pragma unroll
-    for (int j = 0; j < kDPT; ++j) {
-        const int d = t * kDPT + j;
-        if (d < R) {
-            gbase[d] = dbase + hist[(size_t)d * nblocks + blockIdx.x];
-            for (int w = 0; w < 4; ++w) wcnt[w][d] = 0;
+    constexpr int kDPT = R > kListThreads ? R / kListThreads : 1;
+    const int d0 = t * kDPT;
+    const int active = (int)min((uint64_t)0x7FFFFFFF, (count + kTile - 1) / kTile);
+    const int nsup = (active + group - 1) / group;
+    if (seg.block_ranges && blockIdx.x == gridDim.x - 1) {   // the extra workgroup
+        sum_rows<R>(sup, wave, nsup, kWaves, part[wave]);
+        __syncthreads();
+        for (int d = t; d < R; d += kListThreads) {
+            uint32_t c = 0;
+            for (int w = 0; w < kWaves; ++w) c += part[w][d];
+            gbase[d] = c;
         }
-        dbase += dtv[j];
+        __syncthreads();
+        segment_table(gbase, seg);
+        return;
     }
-    __syncthreads();
-    // rank within the wave's slice, in key order
+    if ((uint64_t)blockIdx.x * kTile >= count) return;   // past the keys: nothing to move
+    // the keys' loads first: they are in flight while the counts are added up
     const uint64_t base = (uint64_t)blockIdx.x * kTile;
     const uint64_t wbase = base + (uint64_t)wave * kSlice;
-    uint32_t key[kItems], val[kItems], rank[kItems];
+    uint32_t key[kItems];
+    ValT val[kItems];
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const uint64_t idx = wbase + (uint64_t)i * kWave + lane;
-        const bool valid = idx < count;
-        key[i] = valid ? (uint32_t)keys_in[idx] : 0u;
-        val[i] = valid ? (vals_in ? vals_in[idx] : (uint32_t)idx) : 0u;
+        key[i] = idx < count ? keys_in[idx] : 0u;
     }
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const uint64_t idx = min(wbase + (uint64_t)i * kWave + lane, count - 1);   // no condition: loads together
+        if constexpr (kMode == kFirst) {
+            const uint2 r = splat_rect(splats, (uint32_t)idx);
+            val[i] = make_uint2(r.x, r.y);   // packed below
+        } else if constexpr (sizeof(ValT) == 4) {
+            val[i] = vals_in ? vals_in[idx] : (uint32_t)idx;
+        } else {
+            val[i] = vals_in[idx];
+        }
+    }
+    // 4 waves add up the group sums before this workgroup's group, 4 the others,
+    // 8 the counts of its group before it
+    {
+        const int sb = (int)blockIdx.x / group;
+        if (wave < 4) sum_rows<R>(sup, wave, sb, 4, part[wave]);
+        else if (wave < 8) sum_rows<R>(sup, sb + wave - 4, nsup, 4, part[wave]);
+        else sum_rows<R>(hist, sb * group + wave - 8, (int)blockIdx.x, 8, part[wave]);
+    }
+    __syncthreads();
+    uint32_t tot[kDPT] = {}, before[kDPT] = {}, dsum = 0;
+#pragma unroll
+    for (int j = 0; j < kDPT; ++j)
+        if (d0 + j < R) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const uint32_t b = part[w][d0 + j];
+                before[j] += b + part[8 + w][d0 + j] + part[12 + w][d0 + j];
+                tot[j] += b + part[4 + w][d0 + j];
+            }
+            dsum += tot[j];
+        }
+    uint32_t total;
+    uint32_t dbase = wg_excl_scan_1024(dsum, lds16, &total);   // its barriers end the use of part
+#pragma unroll
+    for (int j = 0; j < kDPT; ++j) {
+        const int d = d0 + j;
+        if (d < R) {
+            gbase[d] = dbase + before[j];
+            for (int w = 0; w < kWaves; ++w) wcnt[w][d] = 0;
+        }
+        dbase += tot[j];
+    }
+    __syncthreads();
+    // rank within the wave's slice, in key order
+    uint32_t rank[kItems];
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const uint64_t idx = wbase + (uint64_t)i * kWave + lane;
@@ -216,89 +337,102 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KeyT* __restrict
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    uint32_t tots[kDPT], tsum = 0;
+    uint32_t tsum = 0;
+#pragma unroll
+    for (int j = 0; j < kDPT; ++j)
+        if (d0 + j < R)
+            for (int w = 0; w < kWaves; ++w) tsum += wcnt[w][d0 + j];
+    uint32_t ls = wg_excl_scan_1024(tsum, lds16, &total);
 #pragma unroll
     for (int j = 0; j < kDPT; ++j) {
-        const int d = t * kDPT + j;
-        uint32_t tot = 0;
+        const int d = d0 + j;
         if (d < R) {
-            for (int w = 0; w < 4; ++w) {
+            gbase[d] -= ls;
+            for (int w = 0; w < kWaves; ++w) {
                 const uint32_t c = wcnt[w][d];
-                wcnt[w][d] = tot;
-                tot += c;
+                wcnt[w][d] = ls;
+                ls += c;
             }
         }
-        tots[j] = tot;
-        tsum += tot;
     }
-    uint32_t ls = block_excl_scan(tsum, lds4, nullptr);
+    __syncthreads();
+    // place in the workgroup's digit order; then the keys and the values go
+    // through one LDS buffer in turn (one each would halve the resident
+    // workgroups), each digit's run to consecutive addresses
+    const uint32_t nvalid = (uint32_t)min((uint64_t)kTile, count - base);
 #pragma unroll
-    for (int j = 0; j < kDPT; ++j) {
-        const int d = t * kDPT + j;
-        if (d < R) lstart[d] = ls;
-        ls += tots[j];
+    for (int i = 0; i < kItems; ++i) {
+        const uint64_t idx = wbase + (uint64_t)i * kWave + lane;
+        if (idx < count) {
+            rank[i] += wcnt[wave][(key[i] >> shift) & (R - 1)];
+            kbuf[rank[i]] = key[i];
+        }
+    }
+    __syncthreads();
+    uint32_t pos[kItems], culled = 0;   // culled: bit i, the key of the i-th key written is ~0
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const uint32_t j = t + i * kListThreads;
+        pos[i] = 0;
+        if (j < nvalid) {
+            const uint32_t k = kbuf[j];
+            pos[i] = gbase[(k >> shift) & (R - 1)] + j;
+            if (keys_out) keys_out[pos[i]] = k;
+            if (kMode == kGather) culled |= (k == 0xFFFFFFFFu ? 1u : 0u) << i;
+        }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const uint64_t idx = wbase + (uint64_t)i * kWave + lane;
-        if (idx < count) {
-            const uint32_t d = (key[i] >> shift) & (R - 1);
-            const uint32_t lp = lstart[d] + wcnt[wave][d] + rank[i];
-            skey[lp] = (KeyT)key[i];
-            sval[lp] = val[i];
-        }
+        if constexpr (kMode == kFirst)
+            val[i] = make_uint2((uint32_t)idx, key[i] != 0xFFFFFFFFu ? pack_rect32(val[i]) : kEmptyRect32);
+        if (idx < count) buf[rank[i]] = val[i];
     }
     __syncthreads();
-    const uint32_t nvalid = (uint32_t)min((uint64_t)kTile, count - base);
-    for (uint32_t j = t; j < nvalid; j += kBlock) {
-        const uint32_t k = skey[j];
-        const uint32_t d = (k >> shift) & (R - 1);
-        const uint32_t pos = gbase[d] + (j - lstart[d]);
-        const uint32_t v = sval[j];
-        if (keys_out) keys_out[pos] = (KeyOutT)k;
-        vals_out[pos] = v;
-        if (rect_out) {
-            // tile rectangle of Gaussian v in sorted order; culled Gaussians
-            // (key ~0, no splat record) get an empty one
-            uint2 r = make_uint2(0u, 0u);
-            if (sizeof(KeyT) == 4 && k != 0xFFFFFFFFu) r = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint32_t*>(rect_src + v) + kSplatRectWord);
-            rect_out[pos] = r;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const uint32_t j = t + i * kListThreads;
+        if (j < nvalid) {
+            const ValT v = buf[j];
+            vals_out[pos[i]] = v;
+            // culled Gaussians (key ~0, no splat record) get an empty rectangle
+            if (kMode == kGather)
+                rect_out[pos[i]] = (culled >> i) & 1u ? make_uint2(0u, 0u) : splat_rect(splats, value_index(v));
         }
     }
 }
 
-// One stable LSD pass over `bits` bits at `shift`; vals_in == nullptr means
-// value = position, keys_out == nullptr drops the keys. The grids are sized
-// for cnt.host keys (the capacity in device mode).
-template <int kBits, int kItems, typename KeyT, typename KeyOutT>
-void radix_pass_t(const KeyT* keys_in, const uint32_t* vals_in, PairCount cnt, int shift, KeyOutT* keys_out,
-                  uint32_t* vals_out, uint32_t* hist, uint32_t* digit_tot, hipStream_t s,
-                  const gs_splat* rect_src = nullptr, uint2* rect_out = nullptr,
-                  SegTable seg = SegTable{nullptr, nullptr, nullptr, nullptr, 0})
+// One stable LSD pass over kBits bits at `shift`. The grids are sized for
+// cnt.host keys (the capacity in device mode). `sup`: this pass's group sums,
+// zeroed.
+template <int kBits, int kItems, typename ValT, int kMode>
+void radix_pass(const uint32_t* keys_in, const ValT* vals_in, PairCount cnt, int shift, uint32_t* keys_out,
+                ValT* vals_out, uint32_t* hist, uint32_t* sup, hipStream_t s, const gs_splat* splats = nullptr,
+                uint2* rect_out = nullptr, SegTable seg = SegTable{nullptr, nullptr, nullptr, nullptr, 0})
 {
-    const int nblocks = (int)std::max<int64_t>(div_up((int64_t)cnt.host, (int64_t)kBlock * kItems), 1);
-    hipLaunchKernelGGL((k_radix_hist<kBits, kItems, KeyT>), dim3(nblocks), dim3(kBlock), 0, s, keys_in, cnt, shift,
-                       hist, nblocks);
-    hipLaunchKernelGGL(k_radix_scan, dim3(1 << kBits), dim3(kBlock), 0, s, hist, nblocks, cnt, kBlock * kItems,
-                       digit_tot);
-    hipLaunchKernelGGL((k_radix_scatter<kBits, kItems, KeyT, KeyOutT>), dim3(nblocks + (seg.block_ranges ? 1 : 0)),
-                       dim3(kBlock), 0, s, keys_in, vals_in, cnt, shift, hist, nblocks, digit_tot, keys_out, vals_out,
-                       rect_src, rect_out, seg);
+    static_assert(kItems <= 32, "one culled bit per key");
+    const int nblocks = (int)std::max<int64_t>(div_up((int64_t)cnt.host, (int64_t)kListThreads * kItems), 1);
+    const int group = radix_group(nblocks);
+    hipLaunchKernelGGL((k_radix_hist<kBits, kItems>), dim3(nblocks), dim3(kListThreads), 0, s, keys_in, cnt, shift, hist, sup,
+                       group);
+    hipLaunchKernelGGL((k_radix_scatter<kBits, kItems, ValT, kMode>), dim3(nblocks + (seg.block_ranges ? 1 : 0)),
+                       dim3(kListThreads), 0, s, keys_in, vals_in, cnt, shift, hist, sup, group, keys_out, vals_out, splats,
+                       rect_out, seg);
 }
 
-// A block-sort pass over `bits` (1..9) bits, 8192 keys per workgroup: twice
-// the depth sort's, for longer runs per digit among the 9-bit digits.
+// A block-sort pass over `bits` (1..9) bits.
 constexpr int kBlockSortBits = 9;
-hipError_t block_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, PairCount cnt, int shift, int bits,
-                            uint32_t* keys_out, uint32_t* vals_out, uint32_t* hist, uint32_t* digit_tot, hipStream_t s,
-                            SegTable seg)
+template <int kItems>
+static hipError_t block_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, PairCount cnt, int shift, int bits,
+                                   uint32_t* keys_out, uint32_t* vals_out, uint32_t* hist, uint32_t* sup,
+                                   hipStream_t s, SegTable seg)
 {
     switch (bits) {
-#define GS_PASS(b)                                                                                                   \
-    case b:                                                                                                          \
-        radix_pass_t<b, kBlockSortItems>(keys_in, vals_in, cnt, shift, keys_out, vals_out, hist, digit_tot, s,     \
-                                         nullptr, nullptr, seg);                                                     \
+#define GS_PASS(b)                                                                                                \
+    case b:                                                                                                       \
+        radix_pass<b, kItems, uint32_t, kPlain>(keys_in, vals_in, cnt, shift, keys_out, vals_out, hist, sup, s,   \
+                                                nullptr, nullptr, seg);                                           \
         break;
         GS_PASS(1) GS_PASS(2) GS_PASS(3) GS_PASS(4) GS_PASS(5) GS_PASS(6) GS_PASS(7) GS_PASS(8) GS_PASS(9)
 #undef GS_PASS
@@ -306,6 +440,12 @@ hipError_t block_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, Pa
     }
     return hipGetLastError();
 }
+
+// Keys per thread of the block sort: 8, or 16 where the capacity tells of
+// millions of entries (about a quarter of the pairs), for longer runs per digit
+// (scatter 12 us with 8 and 18 with 16 at 0.3M entries, 62 and 54 at 6.5M, 104
+// and 82 at 11M).
+static int block_items(uint64_t capacity) { return capacity <= (12u << 20) ? kBlockSortItems : 2 * kBlockSortItems; }
 
 // ---- block entries in depth order -------------------------------------------
 //
@@ -331,24 +471,32 @@ __device__ __forceinline__ uint2 block_rect(uint2 r)
     return make_uint2((x0 >> kS) | ((y0 >> kS) << 16), ((x1 + kR) >> kS) | (((y1 + kR) >> kS) << 16));
 }
 
+// Index and tile rectangle of the i-th Gaussian in depth order.
+template <bool kPacked>
+__device__ __forceinline__ uint2 sorted_rect_at(const DepthOrder& o, int64_t i)
+{
+    return kPacked ? unpack_rect32(o.packed[i].y) : o.rect[i];
+}
+
 // Entries of each chunk of kDupChunk depth-ordered Gaussians.
-__global__ __launch_bounds__(kBlock) void k_entry_partial(const uint2* __restrict__ sorted_rect, int64_t n,
+template <bool kPacked>
+__global__ __launch_bounds__(kBlock) void k_entry_partial(DepthOrder order, int64_t n,
                                                           uint32_t* __restrict__ part)
 {
     __shared__ uint32_t lds4[4];
     uint32_t sum = 0;
     for (int k = 0; k < kDupItems; ++k) {
         const int64_t i = (int64_t)blockIdx.x * kDupChunk + (int64_t)k * kBlock + threadIdx.x;
-        if (i < n) sum += rect_area(block_rect(sorted_rect[i]));
+        if (i < n) sum += rect_area(block_rect(sorted_rect_at<kPacked>(order, i)));
     }
     uint32_t total;
     block_excl_scan(sum, lds4, &total);
     if (threadIdx.x == 0) part[blockIdx.x] = total;
 }
 
-// Exclusive scan of the per-chunk totals (one workgroup); the grand total, the
-// number of entries, goes to *entries (0 when the pair count is over capacity:
-// nothing downstream then reads an entry).
+// Exclusive scan of the per-chunk totals (one workgroup) of more than
+// kSumChunks chunks; the grand total, the number of entries, goes to *entries (0
+// when the pair count is over capacity: nothing downstream then reads an entry).
 __global__ __launch_bounds__(kBlock) void k_scan_partials(uint32_t* __restrict__ part, int count, PairCount pairs,
                                                           uint64_t* __restrict__ entries)
 {
@@ -417,13 +565,22 @@ constexpr int kDupGroups = 8;                   // 64-entry groups per round
 constexpr int kDupWin = kWave * kDupGroups;     // entries per round
 constexpr int kMaskBits = 16;                   // low key bits: the tile mask
 
-__global__ __launch_bounds__(kBlock) void k_block_entries(const uint32_t* __restrict__ order,
-                                                          const uint2* __restrict__ sorted_rect, int64_t n,
+//
+// Up to kSumChunks chunks each workgroup adds up the totals of the chunks before
+// its own (kSum; a few loads per thread, against 5 us and a launch for a scan of
+// them), and the last one stores the number of entries; a larger scene's totals
+// are scanned beforehand, since the sums grow with the square of the chunks.
+constexpr int kSumChunks = 8192;
+
+template <bool kPacked, bool kSum>
+__global__ __launch_bounds__(kBlock) void k_block_entries(DepthOrder order, int64_t n,
                                                           const uint32_t* __restrict__ part, int blocks_x,
-                                                          PairCount entries, uint32_t* __restrict__ keys,
+                                                          PairCount pairs, uint64_t capacity,
+                                                          uint64_t* __restrict__ entries, uint32_t* __restrict__ keys,
                                                           uint32_t* __restrict__ vals)
 {
-    const uint32_t count = (uint32_t)entries.get();   // 0 when the pairs are over capacity
+    // nothing is written when the pairs are over capacity
+    const uint32_t count = pairs.overflow() ? 0u : (uint32_t)capacity;
     __shared__ uint32_t soff[kDupChunk + 1];
     __shared__ uint32_t sorg[kDupChunk];   // block rectangle origin x0 | y0 << 16
     __shared__ uint32_t swid[kDupChunk];   // block rectangle width
@@ -441,8 +598,14 @@ __global__ __launch_bounds__(kBlock) void k_block_entries(const uint32_t* __rest
         uint32_t c = 0, org = 0, w = 1, g = 0;
         uint2 tr = make_uint2(0u, 0u);
         if (i < n) {
-            tr = sorted_rect[i];
-            g = order[i];
+            if (kPacked) {
+                const uint2 v = order.packed[i];
+                g = v.x;
+                tr = unpack_rect32(v.y);
+            } else {
+                g = order.gid[i];
+                tr = order.rect[i];
+            }
             const uint2 r = block_rect(tr);
             c = rect_area(r);
             if (c != 0) {
@@ -465,7 +628,15 @@ __global__ __launch_bounds__(kBlock) void k_block_entries(const uint32_t* __rest
     }
     if (t == 0) soff[kDupChunk] = total;
     __syncthreads();
-    const uint32_t gbase = part[blockIdx.x];
+    uint32_t gbase = 0;
+    if (kSum) {
+        uint32_t before = 0;
+        for (uint32_t k = t; k < blockIdx.x; k += kBlock) before += part[k];
+        block_excl_scan(before, lds4, &gbase);
+        if (blockIdx.x == gridDim.x - 1 && t == 0) *entries = pairs.overflow() ? 0ull : (uint64_t)gbase + total;
+    } else {
+        gbase = part[blockIdx.x];
+    }
     const int wave = t >> 6, lane = __lane_id();
     const uint32_t q0 = (uint32_t)(((uint64_t)total * wave) / (kBlock / kWave));
     const uint32_t q1 = (uint32_t)(((uint64_t)total * (wave + 1)) / (kBlock / kWave));
@@ -527,7 +698,6 @@ __global__ __launch_bounds__(kBlock) void k_block_entries(const uint32_t* __rest
             const uint32_t bx = (org[k] & 0xFFFFu) + (i - q * w[k]);
             const uint32_t by = (org[k] >> 16) + q;
             const uint32_t out = gbase + p;
-            // a count of 0 (pairs over capacity) writes nothing
             if (p < q1 && out < count) {
                 keys[out] = ((by * (uint32_t)blocks_x + bx) << kMaskBits) | tile_mask(tr[k], (int)bx, (int)by);
                 vals[out] = gid[k];
@@ -584,96 +754,39 @@ constexpr int kBlockTiles = kBlockDim * kBlockDim;             // 16
 constexpr int kSegRounds = 8;                                  // 64-entry rounds per wave
 constexpr int kSegEntries = kSegRounds * kBlock;               // 2048 entries per segment
 constexpr int kSubSegs = kBlock / kWave;                       // one sub-segment per wave
-constexpr int kListThreads = 1024;                             // single-workgroup scans
 static_assert(kBlockTiles == 16, "tile masks are 16 bits");
 
-// Exclusive scan of one value per thread over a 1024-thread workgroup.
-template <typename T>
-__device__ __forceinline__ T wg_excl_scan_1024(T v, T* lds16, T* total)
+// Segment table: one workgroup of kListThreads. seg_base[b] = first segment of
+// block b (and seg_base[n_blocks] = their number), seg_block[s] = the block of
+// segment s, counters[0] = the number of segments. block_count (a single-pass
+// block sort's digit totals, which give the ranges too) or nullptr: the ranges
+// are there.
+__device__ void segment_table(const uint32_t* block_count, const SegTable& t)
 {
-    const int lane = __lane_id(), wave = threadIdx.x >> 6;
-    T x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const T y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) lds16[wave] = x;
-    __syncthreads();
-    T before = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kListThreads / kWave; ++w) {
-        const T s = lds16[w];
-        if (w < wave) before += s;
-        tot += s;
-    }
-    __syncthreads();
-    *total = tot;
-    return before + x - v;
-}
-
-// Segment table: one workgroup. seg_base[b] = first segment of block b (and
-// seg_base[n_blocks] = their number), seg_block[s] = the block of segment s,
-// counters[0] = the number of segments.
-__global__ __launch_bounds__(kListThreads) void k_segments(const uint32_t* __restrict__ block_count,
-                                                           uint32_t* __restrict__ block_ranges, int n_blocks,
-                                                           uint32_t* __restrict__ seg_base,
-                                                           uint32_t* __restrict__ seg_block,
-                                                           uint32_t* __restrict__ counters)
-{
-    __shared__ uint32_t lds16[kListThreads / kWave];
+    __shared__ uint32_t lds16s[kListThreads / kWave];
     uint32_t carry = 0, ecarry = 0;
-    for (int b0 = 0; b0 < n_blocks; b0 += kListThreads) {
+    for (int b0 = 0; b0 < t.n_blocks; b0 += kListThreads) {
         const int b = b0 + (int)threadIdx.x;
         uint32_t len = 0;
         if (block_count) {
-            // the ranges follow from the counts (a single-pass block sort's digit totals)
-            len = b < n_blocks ? block_count[b] : 0u;
+            len = b < t.n_blocks ? block_count[b] : 0u;
             uint32_t etotal;
-            const uint32_t start = ecarry + wg_excl_scan_1024(len, lds16, &etotal);
-            if (b < n_blocks) {
-                block_ranges[2 * b] = start;
-                block_ranges[2 * b + 1] = start + len;
+            const uint32_t start = ecarry + wg_excl_scan_1024(len, lds16s, &etotal);
+            if (b < t.n_blocks) {
+                t.block_ranges[2 * b] = start;
+                t.block_ranges[2 * b + 1] = start + len;
             }
             ecarry += etotal;
-        } else if (b < n_blocks) {
-            len = block_ranges[2 * b + 1] - block_ranges[2 * b];
+        } else if (b < t.n_blocks) {
+            len = t.block_ranges[2 * b + 1] - t.block_ranges[2 * b];
         }
         const uint32_t ns = (len + kSegEntries - 1) / kSegEntries;
         uint32_t total;
-        const uint32_t first = carry + wg_excl_scan_1024(ns, lds16, &total);
-        if (b < n_blocks) {
-            seg_base[b] = first;
-            for (uint32_t k = 0; k < ns; ++k) seg_block[first + k] = (uint32_t)b;
-        }
-        carry += total;
-    }
-    if (threadIdx.x == 0) {
-        seg_base[n_blocks] = carry;
-        counters[0] = carry;
-    }
-}
-
-// k_segments' table from the digit totals of a single-pass block sort, for
-// one 256-thread workgroup (the block sort scatter's extra one).
-__device__ void segment_table_256(const uint32_t* __restrict__ block_count, const SegTable& t)
-{
-    __shared__ uint32_t lds4s[4];
-    uint32_t carry = 0, ecarry = 0;
-    for (int b0 = 0; b0 < t.n_blocks; b0 += kBlock) {
-        const int b = b0 + (int)threadIdx.x;
-        const uint32_t len = b < t.n_blocks ? block_count[b] : 0u;
-        uint32_t etotal, total;
-        const uint32_t start = ecarry + block_excl_scan(len, lds4s, &etotal);
-        const uint32_t ns = (len + kSegEntries - 1) / kSegEntries;
-        const uint32_t first = carry + block_excl_scan(ns, lds4s, &total);
+        const uint32_t first = carry + wg_excl_scan_1024(ns, lds16s, &total);
         if (b < t.n_blocks) {
-            t.block_ranges[2 * b] = start;
-            t.block_ranges[2 * b + 1] = start + len;
             t.seg_base[b] = first;
             for (uint32_t k = 0; k < ns; ++k) t.seg_block[first + k] = (uint32_t)b;
         }
-        ecarry += etotal;
         carry += total;
     }
     if (threadIdx.x == 0) {
@@ -681,6 +794,8 @@ __device__ void segment_table_256(const uint32_t* __restrict__ block_count, cons
         t.counters[0] = carry;
     }
 }
+
+__global__ __launch_bounds__(kListThreads) void k_segments(SegTable t) { segment_table(nullptr, t); }
 
 // The entry range of segment s: block b, entries [e0, e1).
 struct Segment {
@@ -891,30 +1006,77 @@ __global__ __launch_bounds__(kBlock) void k_tile_emit(const uint32_t* __restrict
 
 }  // namespace
 
-hipError_t launch_depth_sort(int64_t n, const uint32_t* depth_key, const gs_splat* splats, const Workspace& ws,
-                             const uint32_t** order_out, hipStream_t s)
+// Workgroups per group sum of a radix pass: the rows a workgroup adds up, group
+// sums and then counts, are fewest near the square root.
+int radix_group(int nblocks)
 {
-    const uint32_t* kin = depth_key;
-    const uint32_t* vin = nullptr;
+    int g = 1;
+    while ((int64_t)g * g < nblocks) ++g;
+    return g;
+}
+
+int radix_groups(int64_t keys, int tile)
+{
+    const int nblocks = (int)std::max<int64_t>(div_up(keys, tile), 1);
+    return (int)div_up(nblocks, radix_group(nblocks));
+}
+
+// Keys per thread of the depth sort's passes (1,024 threads): the fewest that
+// make at most one workgroup per compute unit, so that every unit works and a
+// digit's runs are as long as that allows; 12 for more keys than that (scatters
+// at 3M Gaussians: 145 us with 8, 118 with 12; at 6M 290 with 8, 273 with 12,
+// 319 with 16, which spill).
+int depth_items(int64_t n) { return n <= (1 << 20) ? 4 : n <= (1 << 21) ? 8 : 12; }
+
+// Depth sort of the n Gaussians and their tile rectangles. On grids of at most
+// 256 x 256 tiles the rectangles travel with the sort in 32 bits, read from the
+// records in index order by the first pass: 4 bytes more per Gaussian and pass,
+// where the last pass would otherwise gather one 128-byte line per Gaussian
+// (60 us of that pass's 78 at 3M Gaussians, 155 at 6M).
+bool packed_rects(const Cam& cam) { return cam.tiles_x <= 256 && cam.tiles_y <= 256; }
+
+template <int kItems>
+static void depth_passes(const Cam& cam, int64_t n, const uint32_t* depth_key, const gs_splat* splats,
+                         const Workspace& ws, DepthOrder* out, hipStream_t s)
+{
     uint32_t* kbuf[2] = {ws.keys_a, ws.keys_b};
-    uint32_t* vbuf[2] = {ws.vals_a, ws.vals_b};
     const PairCount keys_n{nullptr, (uint64_t)n, (uint64_t)n};
-    for (int p = 0; p < 4; ++p) {
-        const bool last = p == 3;
-        uint32_t* kout = last ? nullptr : kbuf[p & 1];
-        if (last)
-            radix_pass_t<8, kSortItems>(kin, vin, keys_n, 8 * p, (uint32_t*)nullptr, vbuf[p & 1], ws.hist,
-                                        ws.digit_tot + kRadix * p, s, splats, ws.sorted_rect);
-        else
-            radix_pass_t<8, kSortItems>(kin, vin, keys_n, 8 * p, kout, vbuf[p & 1], ws.hist,
-                                        ws.digit_tot + kRadix * p, s);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        kin = kbuf[p & 1];
-        vin = vbuf[p & 1];
+    const int groups = radix_groups(n, kListThreads * kItems);
+    auto sup = [&](int p) { return ws.depth_sup + (size_t)p * groups * kRadix; };
+    *out = DepthOrder{nullptr, nullptr, nullptr};
+    if (packed_rects(cam)) {
+        uint2* vbuf[2] = {ws.vals_a, ws.vals_b};
+        radix_pass<8, kItems, uint2, kFirst>(depth_key, nullptr, keys_n, 0, kbuf[0], vbuf[0], ws.hist, sup(0), s,
+                                             splats);
+        for (int p = 1; p < 4; ++p)
+            radix_pass<8, kItems, uint2, kPlain>(kbuf[(p & 1) ^ 1], vbuf[(p & 1) ^ 1], keys_n, 8 * p,
+                                                 p == 3 ? nullptr : kbuf[p & 1], vbuf[p & 1], ws.hist, sup(p), s);
+        out->packed = vbuf[1];
+    } else {
+        // indices alone: both buffers in one of the pair buffers, the rectangles in the other
+        uint32_t* vbuf[2] = {reinterpret_cast<uint32_t*>(ws.vals_a), reinterpret_cast<uint32_t*>(ws.vals_a) + n};
+        for (int p = 0; p < 3; ++p)
+            radix_pass<8, kItems, uint32_t, kPlain>(p == 0 ? depth_key : kbuf[(p & 1) ^ 1],
+                                                    p == 0 ? nullptr : vbuf[(p & 1) ^ 1], keys_n, 8 * p, kbuf[p & 1],
+                                                    vbuf[p & 1], ws.hist, sup(p), s);
+        radix_pass<8, kItems, uint32_t, kGather>(kbuf[0], vbuf[0], keys_n, 24, nullptr, vbuf[1], ws.hist, sup(3), s,
+                                                 splats, ws.vals_b);
+        out->gid = vbuf[1];
+        out->rect = ws.vals_b;
     }
-    *order_out = vin;
-    return hipSuccess;
+}
+
+hipError_t launch_depth_sort(const Cam& cam, int64_t n, const uint32_t* depth_key, const gs_splat* splats,
+                             const Workspace& ws, DepthOrder* out, hipStream_t s)
+{
+    const hipError_t e = launch_fill_u32(ws.depth_sup, ws.sup_count, 0u, s);   // the block sort's too
+    if (e != hipSuccess) return e;
+    switch (depth_items(n)) {
+    case 4: depth_passes<4>(cam, n, depth_key, splats, ws, out, s); break;
+    case 8: depth_passes<8>(cam, n, depth_key, splats, ws, out, s); break;
+    default: depth_passes<12>(cam, n, depth_key, splats, ws, out, s); break;
+    }
+    return hipGetLastError();
 }
 
 int blocks_x_of(const Cam& cam) { return (cam.tiles_x + kBlockDim - 1) / kBlockDim; }
@@ -924,11 +1086,17 @@ int64_t segment_bound(const Cam& cam, uint64_t capacity)
     return div_up((int64_t)capacity, kSegEntries) + (int64_t)blocks_x_of(cam) * blocks_y_of(cam);
 }
 
-hipError_t launch_entry_offsets(int64_t n, PairCount pairs, const Workspace& ws, hipStream_t s)
+hipError_t launch_entry_offsets(int64_t n, PairCount pairs, const DepthOrder& order, const Workspace& ws,
+                                hipStream_t s)
 {
     const int nb = (int)div_up(n, kDupChunk);
-    hipLaunchKernelGGL(k_entry_partial, dim3(nb), dim3(kBlock), 0, s, ws.sorted_rect, n, ws.scan_part);
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, ws.scan_part, nb, pairs, ws.entry_count);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, order, n, ws.scan_part);
+    };
+    if (order.packed) launch(k_entry_partial<true>);
+    else launch(k_entry_partial<false>);
+    if (nb > kSumChunks)
+        hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, ws.scan_part, nb, pairs, ws.entry_count);
     return hipGetLastError();
 }
 
@@ -943,12 +1111,17 @@ static int block_bits(const Cam& cam)
 
 bool blocks_supported(const Cam& cam) { return block_bits(cam) <= 32 - kMaskBits; }
 
-hipError_t launch_block_entries(const Cam& cam, int64_t n, const uint32_t* order, PairCount entries,
-                                const Workspace& ws, hipStream_t s)
+hipError_t launch_block_entries(const Cam& cam, int64_t n, const DepthOrder& order, PairCount pairs,
+                                uint64_t capacity, const Workspace& ws, hipStream_t s)
 {
     const int nb = (int)div_up(n, kDupChunk);
-    hipLaunchKernelGGL(k_block_entries, dim3(nb), dim3(kBlock), 0, s, order, ws.sorted_rect, n, ws.scan_part,
-                       blocks_x_of(cam), entries, ws.entry_keys_a, ws.entry_vals_a);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, s, order, n, ws.scan_part, blocks_x_of(cam),
+                           pairs, capacity, ws.entry_count, ws.entry_keys_a, ws.entry_vals_a);
+    };
+    const bool sum = nb <= kSumChunks;
+    if (order.packed) sum ? launch(k_block_entries<true, true>) : launch(k_block_entries<true, false>);
+    else sum ? launch(k_block_entries<false, true>) : launch(k_block_entries<false, false>);
     return hipGetLastError();
 }
 
@@ -961,6 +1134,7 @@ hipError_t launch_block_sort(const Cam& cam, PairCount entries, const Workspace&
     const int n_blocks = blocks_x_of(cam) * blocks_y_of(cam);
     const int bits = block_bits(cam);
     const int passes = (bits + kBlockSortBits - 1) / kBlockSortBits;
+    const int items = block_items(entries.host);
     uint32_t* kbuf[2] = {ws.entry_keys_a, ws.entry_keys_b};
     uint32_t* vbuf[2] = {ws.entry_vals_a, ws.entry_vals_b};
     int src = 0, shift = kMaskBits;
@@ -970,9 +1144,10 @@ hipError_t launch_block_sort(const Cam& cam, PairCount entries, const Workspace&
     const SegTable seg_none{nullptr, nullptr, nullptr, nullptr, 0};
     for (int p = 0; p < passes; ++p) {
         const int pb = (kMaskBits + bits - shift + (passes - p) - 1) / (passes - p);   // remaining bits spread evenly
-        const hipError_t e = block_radix_pass(kbuf[src], vbuf[src], entries, shift, pb, kbuf[src ^ 1],
-                                              vbuf[src ^ 1], ws.hist, ws.digit_tot, s,
-                                              passes == 1 ? seg_one : seg_none);
+        uint32_t* sup = ws.block_sup + (size_t)p * radix_groups((int64_t)entries.host, kListThreads * items) * 2 * kRadix;
+        auto pass = items == kBlockSortItems ? block_radix_pass<kBlockSortItems> : block_radix_pass<2 * kBlockSortItems>;
+        const hipError_t e = pass(kbuf[src], vbuf[src], entries, shift, pb, kbuf[src ^ 1], vbuf[src ^ 1], ws.hist, sup,
+                                  s, passes == 1 ? seg_one : seg_none);
         if (e != hipSuccess) return e;
         shift += pb;
         src ^= 1;
@@ -981,8 +1156,7 @@ hipError_t launch_block_sort(const Cam& cam, PairCount entries, const Workspace&
         const dim3 grid((unsigned)div_up(n_blocks + 1, kBlock / kWave));
         hipLaunchKernelGGL(k_ranges, grid, dim3(kBlock), 0, s, kbuf[src], kMaskBits, entries, n_blocks,
                            ws.block_ranges);
-        hipLaunchKernelGGL(k_segments, dim3(1), dim3(kListThreads), 0, s, (const uint32_t*)nullptr,
-                           ws.block_ranges, n_blocks, ws.seg_base, ws.seg_block, ws.list_counters);
+        hipLaunchKernelGGL(k_segments, dim3(1), dim3(kListThreads), 0, s, seg_one);
     }
     out->key = kbuf[src];
     out->gid = vbuf[src];

@@ -95,6 +95,25 @@ def test_more_than_65536_tiles():
     check_all(sc, tiny_camera(16 * 4097, 256), label="wide", grads=False)
 
 
+@pytest.mark.parametrize("n,size", [(4097, (4096, 48)), (8193, (4097, 48)), (1 << 20, (64, 4096)),
+                                    ((1 << 20) + 1, (64, 4097)), ((1 << 21) + 4097, (320, 240))])
+def test_depth_sort_workgroups(n, size):
+    # 4, 8 and 12 keys per thread of the depth sort's passes (to 2^20, to 2^21,
+    # above), workgroups that are full, hold one key, or end inside a wave; tile
+    # grids of 256 and 257 tiles a side, with rectangles packed in 32 bits or
+    # gathered; equal depths (ties by index) and culled Gaussians among them
+    sc = inputs.make_scene("tiny", n=n)
+    sc.means[:, ::3] = np.round(sc.means[:, ::3] * 4) / 4
+    sc.means[2, ::11] = -4.0
+    cam = tiny_camera(*size)
+    sc.log_scales[:] = np.float32(np.log(20.0 / cam.fx) if n < 10000 else np.log(0.1 / cam.fx))
+    # the capacity also picks 8 (up to 12 << 20 pairs) or 16 entries per thread of the block sort
+    gpu = run_gpu(sc, cam, capacity=1 << 18 if n < 10000 else 1 << 25)
+    pre = orc.preprocess(cam, sc)
+    values, tiles, ranges = orc.bin_sort(cam, pre)
+    compare_lists(gpu, values, tiles, ranges)
+
+
 @pytest.mark.parametrize("tiles_x", [2048, 2049])
 def test_backward_tile_order_limit(tiles_x):
     # 2048 x 16 = 32768 tiles, the largest image whose backward launches its
