@@ -444,9 +444,17 @@ gs_status gs_bin_sort(const gs_camera* cam, const gs_preprocessed* pre, int64_t 
     const PairCount entries{ws.entry_count, capacity, capacity};
     DepthOrder order{nullptr, nullptr, nullptr};
     BlockEntries ent{nullptr, nullptr};
+    const bool small = small_lists(c, n);
     timing_begin(GS_KERNEL_DEPTH_SORT, s);
+    if (!small || !small_depth_sort(c, n)) GS_HIP(launch_clear_sums(ws, s));
     GS_HIP(launch_depth_sort(c, n, pre->depth_key, pre->splats, ws, &order, s));
     timing_end(GS_KERNEL_DEPTH_SORT, s);
+    if (small) {
+        timing_begin(GS_KERNEL_TILE_LISTS, s);
+        GS_HIP(launch_small_lists(c, n, order, pairs, capacity, ws, values, tile_ids, tile_ranges, s));
+        timing_end(GS_KERNEL_TILE_LISTS, s);
+        return ok();
+    }
     timing_begin(GS_KERNEL_ENTRY_OFFSETS, s);
     GS_HIP(launch_entry_offsets(n, pairs, order, ws, s));
     timing_end(GS_KERNEL_ENTRY_OFFSETS, s);

@@ -105,7 +105,7 @@ struct Workspace {
     uint32_t* seg_cnt;       // [segments][4][16] per-tile counts, then offsets, of each wave's sub-segment
     uint32_t* list_counters; // [2]               segments; tile lists over capacity
     float* acc;              // [n][9]            blend-backward accumulators
-    uint32_t* walk_cls;      // [tiles]           walk-length class of each tile (blend backward)
+    uint32_t* walk_cls;      // [tiles]           walk-length class of each tile (blend backward); tile lengths (few Gaussians)
     uint32_t* tile_order;    // [tiles]           tiles, longest walk first (blend backward)
     float* mlp_part;         // [kMlpPartials][1664] per-workgroup decoder weight gradients
     size_t bytes;
@@ -164,6 +164,15 @@ hipError_t launch_block_sort(const Cam& cam, PairCount entries, const Workspace&
 hipError_t launch_tile_lists(const Cam& cam, PairCount pairs, uint64_t capacity, const Workspace& ws,
                              const BlockEntries& ent, uint32_t* values, uint32_t* tile_ids, uint32_t* tile_ranges,
                              hipStream_t s);
+// Clears the radix passes' group sums (once per call, before the first pass).
+hipError_t launch_clear_sums(const Workspace& ws, hipStream_t s);
+bool small_depth_sort(const Cam& cam, int64_t n);   // the depth sort of few Gaussians, which has no passes
+// Few Gaussians (small_lists): the tile lists from the depth order in two
+// launches, without block entries; the tile lengths in ws.walk_cls.
+bool small_lists(const Cam& cam, int64_t n);
+hipError_t launch_small_lists(const Cam& cam, int64_t n, const DepthOrder& order, PairCount pairs, uint64_t capacity,
+                              const Workspace& ws, uint32_t* values, uint32_t* tile_ids, uint32_t* tile_ranges,
+                              hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream_t s);
 hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32_t* values,
                             const uint32_t* tile_ranges, float* image, float* final_T, uint32_t* n_contrib,

@@ -1004,6 +1004,215 @@ __global__ __launch_bounds__(kBlock) void k_tile_emit(const uint32_t* __restrict
     }
 }
 
+// ---- few Gaussians ------------------------------------------------------------
+//
+// With few Gaussians the path above is bound by its 17 launches (4 to 5 us each).
+// Up to kSmallSort one workgroup sorts the Gaussians by depth in LDS instead (11
+// us at 1,024, 46 at 12,000; the passes above take 57 and 69 there, and overtake
+// it where a workgroup's registers run out). Up to kSmallMax one workgroup per
+// 4x4-tile block then finds the block's entries among all Gaussians, twice: to
+// count its tile lists and to write them. Binning 1,024 Gaussians into 16 tiles
+// takes 28 us in three launches (103 before), 12,000 into 1,200 tiles 74 (136).
+// Both are for grids whose rectangles are packed.
+constexpr int kSmallSortItems = 12, kSmallItems = 24;             // keys per thread
+constexpr int64_t kSmallSort = (int64_t)kListThreads * kSmallSortItems;
+constexpr int64_t kSmallMax = (int64_t)kListThreads * kSmallItems;
+constexpr int64_t kSmallTiles = 16384;                            // tiles whose lengths a block adds up
+constexpr int64_t kSmallWork = 16 << 20;                          // Gaussians times blocks
+
+template <int kItems>
+__global__ __launch_bounds__(kListThreads) void k_small_depth_sort(const uint32_t* __restrict__ depth_key,
+                                                                   const gs_splat* __restrict__ splats, int n,
+                                                                   uint2* __restrict__ out)
+{
+    constexpr int R = kRadix, kWaves = kListThreads / kWave, kSlice = kWave * kItems;
+    __shared__ uint32_t wcnt[kWaves][R];
+    __shared__ uint32_t buf[kListThreads * kItems];
+    __shared__ uint32_t lds16[kWaves];
+    const int t = threadIdx.x, wave = t >> 6, lane = __lane_id();
+    const int base = wave * kSlice + lane;
+    static_assert(kListThreads * kItems <= 1 << 15, "index and rank share a register");
+    uint32_t key[kItems], vr[kItems];   // vr: index | rank << 16
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int idx = base + i * kWave;
+        key[i] = idx < n ? depth_key[idx] : 0u;
+        vr[i] = (uint32_t)idx;
+    }
+#pragma unroll 1
+    for (int shift = 0; shift < 32; shift += 8) {
+        for (int k = t; k < kWaves * R; k += kListThreads) (&wcnt[0][0])[k] = 0;
+        __syncthreads();
+        // stable ranks, as in k_radix_scatter
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            const bool valid = base + i * kWave < n;
+            const uint32_t d = (key[i] >> shift) & (R - 1);
+            const uint64_t peers = match_digit<8>(d, valid);
+            const uint32_t r = (uint32_t)__popcll(peers & lanemask_lt());
+            const uint32_t pre = valid ? wcnt[wave][d] : 0u;
+            vr[i] |= (pre + r) << 16;
+            if (valid && r == 0) wcnt[wave][d] = pre + (uint32_t)__popcll(peers);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        uint32_t sum = 0, total;
+        if (t < R)
+            for (int w = 0; w < kWaves; ++w) sum += wcnt[w][t];
+        uint32_t first = wg_excl_scan_1024(sum, lds16, &total);
+        if (t < R)
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t c = wcnt[w][t];
+                wcnt[w][t] = first;
+                first += c;
+            }
+        __syncthreads();
+        // the keys, then the values, through one buffer into their new places
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+            if (base + i * kWave < n) {
+                vr[i] += wcnt[wave][(key[i] >> shift) & (R - 1)] << 16;
+                buf[vr[i] >> 16] = key[i];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+            if (base + i * kWave < n) key[i] = buf[base + i * kWave];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+            if (base + i * kWave < n) buf[vr[i] >> 16] = vr[i] & 0xFFFFu;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+            if (base + i * kWave < n) vr[i] = buf[base + i * kWave];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int pos = base + i * kWave;
+        if (pos < n) {
+            const uint2 r = splat_rect(splats, vr[i]);
+            out[pos] = make_uint2(vr[i], key[i] != 0xFFFFFFFFu ? pack_rect32(r) : kEmptyRect32);
+        }
+    }
+}
+
+// One workgroup per block, one wave per tile of it. The Gaussians that meet the
+// block are compacted, in depth order, into LDS (position and mask of the
+// block's tiles); each wave then counts those of its tile (kEmit false: into
+// tile_len) or writes them (kEmit true), at the sum of the lengths of the tiles
+// before, which every workgroup adds up for its own four rows of tiles. Pairs
+// over the capacity (the preprocess's count, or the lengths' sum) leave every
+// range empty.
+template <int kItems, bool kEmit>
+__global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __restrict__ order, int n,
+                                                              int blocks_x,
+                                                              int tiles_x, int tiles_y, uint32_t* __restrict__ tile_len,
+                                                              PairCount pairs, uint64_t capacity,
+                                                              uint32_t* __restrict__ values,
+                                                              uint32_t* __restrict__ tile_ids,
+                                                              uint32_t* __restrict__ tile_ranges)
+{
+    constexpr int kWaves = kListThreads / kWave, kSlice = kWave * kItems;
+    static_assert(kWaves == kBlockDim * kBlockDim, "a wave per tile");
+    __shared__ uint16_t smask[kListThreads * kItems];
+    __shared__ uint32_t list[kListThreads * kItems];
+    __shared__ uint32_t wcount[kWaves];
+    __shared__ uint64_t sums[kWaves][kBlockDim + 1];
+    const int t = threadIdx.x, wave = t >> 6, lane = __lane_id();
+    const int bx = (int)blockIdx.x % blocks_x, by = (int)blockIdx.x / blocks_x;
+    // masks of this wave's slice of the Gaussians
+    uint32_t found = 0;
+    const int w0 = wave * kSlice, w1 = min(w0 + kSlice, n);
+    for (int i0 = w0; i0 < w1; i0 += 4 * kWave) {
+        uint2 r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kWave + lane;
+            r[u] = i < w1 ? unpack_rect32(order[i].y) : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kWave + lane;
+            const uint32_t m = tile_mask(r[u], bx, by);
+            if (i < w1) smask[i] = (uint16_t)m;
+            found += (uint32_t)__popcll(__ballot(m != 0));
+        }
+    }
+    if (lane == 0) wcount[wave] = found;
+    // lengths of the tiles before each row of this block's, and of all tiles
+    if (kEmit) {
+        uint64_t s[kBlockDim + 1] = {};
+        const int n_tiles = tiles_x * tiles_y;
+        for (int k = t; k < n_tiles; k += kListThreads) {
+            const uint32_t len = tile_len[k];
+#pragma unroll
+            for (int r = 0; r < kBlockDim; ++r)
+                s[r] += k < (kBlockDim * by + r) * tiles_x + kBlockDim * bx ? len : 0u;
+            s[kBlockDim] += len;
+        }
+#pragma unroll
+        for (int r = 0; r <= kBlockDim; ++r) {
+            for (int o = 32; o > 0; o >>= 1) s[r] += __shfl_xor(s[r], o);
+            if (lane == 0) sums[wave][r] = s[r];
+        }
+    }
+    __syncthreads();
+    uint32_t at = 0, m_all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        at += w < wave ? wcount[w] : 0u;
+        m_all += wcount[w];
+    }
+    for (int i0 = w0; i0 < w1; i0 += kWave) {
+        const int i = i0 + lane;
+        const uint32_t m = i < w1 ? smask[i] : 0u;
+        const uint64_t b = __ballot(m != 0);
+        if (m != 0) list[at + (uint32_t)__popcll(b & lanemask_lt())] = (uint32_t)i | (m << 16);
+        at += (uint32_t)__popcll(b);
+    }
+    __syncthreads();
+    const int tx = kBlockDim * bx + (wave & 3), ty = kBlockDim * by + (wave >> 2);
+    if (tx >= tiles_x || ty >= tiles_y) return;
+    const int tile = ty * tiles_x + tx;
+    if (!kEmit) {
+        uint32_t c = 0;
+        for (uint32_t e0 = 0; e0 < m_all; e0 += kWave) {
+            const uint32_t e = e0 + lane;
+            c += (uint32_t)__popcll(__ballot(e < m_all && (list[e] >> (16 + wave)) & 1u));
+        }
+        if (lane == 0) tile_len[tile] = c;
+    } else {
+        uint64_t start = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            start += sums[w][wave >> 2];
+            total += sums[w][kBlockDim];
+        }
+        for (int k = 0; k < (wave & 3); ++k) start += tile_len[tile - (wave & 3) + k];
+        const bool over = pairs.overflow() || total > capacity;
+        uint32_t pos = (uint32_t)start;
+        for (uint32_t e0 = 0; e0 < m_all && !over; e0 += kWave) {
+            const uint32_t e = e0 + lane;
+            const uint32_t v = e < m_all ? list[e] : 0u;
+            const bool on = (v >> (16 + wave)) & 1u;
+            const uint64_t b = __ballot(on);
+            if (on) {
+                const uint32_t q = pos + (uint32_t)__popcll(b & lanemask_lt());
+                values[q] = order[v & 0xFFFFu].x;
+                if (tile_ids) tile_ids[q] = (uint32_t)tile;
+            }
+            pos += (uint32_t)__popcll(b);
+        }
+        if (lane == 0) {
+            tile_ranges[2 * tile] = over ? 0u : (uint32_t)start;
+            tile_ranges[2 * tile + 1] = over ? 0u : pos;
+        }
+    }
+}
+
 }  // namespace
 
 // Workgroups per group sum of a radix pass: the rows a workgroup adds up, group
@@ -1064,19 +1273,6 @@ static void depth_passes(const Cam& cam, int64_t n, const uint32_t* depth_key, c
         out->gid = vbuf[1];
         out->rect = ws.vals_b;
     }
-}
-
-hipError_t launch_depth_sort(const Cam& cam, int64_t n, const uint32_t* depth_key, const gs_splat* splats,
-                             const Workspace& ws, DepthOrder* out, hipStream_t s)
-{
-    const hipError_t e = launch_fill_u32(ws.depth_sup, ws.sup_count, 0u, s);   // the block sort's too
-    if (e != hipSuccess) return e;
-    switch (depth_items(n)) {
-    case 4: depth_passes<4>(cam, n, depth_key, splats, ws, out, s); break;
-    case 8: depth_passes<8>(cam, n, depth_key, splats, ws, out, s); break;
-    default: depth_passes<12>(cam, n, depth_key, splats, ws, out, s); break;
-    }
-    return hipGetLastError();
 }
 
 int blocks_x_of(const Cam& cam) { return (cam.tiles_x + kBlockDim - 1) / kBlockDim; }
@@ -1184,6 +1380,70 @@ hipError_t launch_tile_lists(const Cam& cam, PairCount pairs, uint64_t capacity,
         hipLaunchKernelGGL(k_tile_emit<false>, segs, dim3(kBlock), 0, s, ent.key, ent.gid, ws.block_ranges,
                            ws.seg_base, ws.seg_block, ws.list_counters, bx, cam.tiles_x, ws.seg_cnt, tile_ranges,
                            values, tile_ids);
+    return hipGetLastError();
+}
+
+// Whether the tile lists come from small_lists: within its LDS, and where the
+// blocks' search of all Gaussians costs less than the launches it saves (up to
+// kSmallWork tests: 12,000 Gaussians in 510 blocks 32 us for the two launches,
+// 24,000 in 510 61, against 84 to 88 for the general path's).
+bool small_lists(const Cam& cam, int64_t n)
+{
+    return n <= kSmallMax && packed_rects(cam) && (int64_t)cam.tiles_x * cam.tiles_y <= kSmallTiles &&
+           n * blocks_x_of(cam) * blocks_y_of(cam) <= kSmallWork;
+}
+
+template <int kItems>
+static void small_depth(int n, const uint32_t* depth_key, const gs_splat* splats, uint2* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_small_depth_sort<kItems>, dim3(1), dim3(kListThreads), 0, s, depth_key, splats, n, out);
+}
+
+template <int kItems>
+static void small_tiles(const Cam& cam, int n, const uint2* order, PairCount pairs, uint64_t capacity,
+                        uint32_t* tile_len, uint32_t* values, uint32_t* tile_ids, uint32_t* tile_ranges, hipStream_t s)
+{
+    const int bx = blocks_x_of(cam);
+    const dim3 blocks((unsigned)(bx * blocks_y_of(cam)));
+    hipLaunchKernelGGL((k_small_lists<kItems, false>), blocks, dim3(kListThreads), 0, s, order, n, bx, cam.tiles_x,
+                       cam.tiles_y, tile_len, pairs, capacity, values, tile_ids, tile_ranges);
+    hipLaunchKernelGGL((k_small_lists<kItems, true>), blocks, dim3(kListThreads), 0, s, order, n, bx, cam.tiles_x,
+                       cam.tiles_y, tile_len, pairs, capacity, values, tile_ids, tile_ranges);
+}
+
+hipError_t launch_small_lists(const Cam& cam, int64_t n, const DepthOrder& order, PairCount pairs, uint64_t capacity,
+                              const Workspace& ws, uint32_t* values, uint32_t* tile_ids, uint32_t* tile_ranges,
+                              hipStream_t s)
+{
+    auto f = n <= kListThreads ? small_tiles<1> : n <= 4 * kListThreads ? small_tiles<4>
+             : n <= 12 * kListThreads ? small_tiles<12> : small_tiles<kSmallItems>;
+    f(cam, (int)n, order.packed, pairs, capacity, ws.walk_cls, values, tile_ids, tile_ranges, s);
+    return hipGetLastError();
+}
+
+bool small_depth_sort(const Cam& cam, int64_t n) { return n <= kSmallSort && packed_rects(cam); }
+
+hipError_t launch_clear_sums(const Workspace& ws, hipStream_t s)
+{
+    return launch_fill_u32(ws.depth_sup, ws.sup_count, 0u, s);   // the block sort's lie behind the depth sort's
+}
+
+hipError_t launch_depth_sort(const Cam& cam, int64_t n, const uint32_t* depth_key, const gs_splat* splats,
+                             const Workspace& ws, DepthOrder* out, hipStream_t s)
+{
+    if (small_depth_sort(cam, n)) {
+        auto f = n <= kListThreads ? small_depth<1> : n <= 2 * kListThreads ? small_depth<2>
+                 : n <= 4 * kListThreads ? small_depth<4> : n <= 8 * kListThreads ? small_depth<8>
+                 : small_depth<kSmallSortItems>;
+        f((int)n, depth_key, splats, ws.vals_b, s);
+        *out = DepthOrder{ws.vals_b, nullptr, nullptr};
+        return hipGetLastError();
+    }
+    switch (depth_items(n)) {
+    case 4: depth_passes<4>(cam, n, depth_key, splats, ws, out, s); break;
+    case 8: depth_passes<8>(cam, n, depth_key, splats, ws, out, s); break;
+    default: depth_passes<12>(cam, n, depth_key, splats, ws, out, s); break;
+    }
     return hipGetLastError();
 }
 

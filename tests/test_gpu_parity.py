@@ -114,6 +114,40 @@ def test_depth_sort_workgroups(n, size):
     compare_lists(gpu, values, tiles, ranges)
 
 
+@pytest.mark.parametrize("n,size", [(1, (64, 64)), (1023, (64, 64)), (1025, (200, 90)), (2049, (200, 90)),
+                                    (4097, (1000, 30)), (8193, (330, 200)),
+                                    (12288, (330, 200)), (12289, (330, 200)), (24576, (640, 300)), (24577, (640, 300)),
+                                    (12288, (4096, 1376)), (20000, (1920, 1080)), (3000, (2064, 2064))])
+def test_few_gaussians_binning(n, size):
+    # 1 to 12 Gaussians per thread of the sort, 1 to 24 of the search; the largest counts of the one-workgroup
+    # depth sort and of the blocks' search, and the next; Gaussians times blocks at,
+    # below and above its limit of 2^24; more tiles than it adds up; ties, culled
+    # Gaussians, splats of many blocks; device and host mode, a capacity too small
+    sc = inputs.make_scene("tiny", n=n)
+    sc.means[:, ::3] = np.round(sc.means[:, ::3] * 4) / 4
+    sc.means[2, 5::11] = -4.0
+    cam = tiny_camera(*size)
+    sc.log_scales[:] = np.float32(np.log(8.0 / cam.fx))
+    sc.log_scales[:, ::97] = np.float32(np.log(60.0 / cam.fx))
+    gpu = run_gpu(sc, cam, capacity=1 << 22)
+    pre = orc.preprocess(cam, sc)
+    values, tiles, ranges = orc.bin_sort(cam, pre)
+    compare_lists(gpu, values, tiles, ranges)
+    cs, st, P = gs.camera_struct(cam), gpu["scene_tensors"], gpu["P"]
+    for capacity in (P, P - 1) if P > 1 else ():
+        fr = gs.Frame(n, cam.width, cam.height, gs.GS_APP_SH3, max(capacity, 1))
+        gs.gs_preprocess(cs, st.gaussians(), st.appearance(gs.GS_APP_SH3), fr.pre, fr.workspace, fr.ws_bytes,
+                         sync_pairs=False)
+        gs.gs_bin_sort(cs, fr.pre, n, gs.GS_PAIRS_ON_DEVICE, capacity, fr.values, None, fr.ranges, fr.workspace,
+                       fr.ws_bytes)
+        got = fr.ranges.cpu().numpy().reshape(-1, 2).astype(np.int64)
+        if capacity == P:
+            assert np.array_equal(got, ranges)
+            assert np.array_equal(fr.values.cpu().numpy()[:P].astype(np.int64), values.astype(np.int64))
+        else:
+            assert not got.any() and int(fr.num_pairs.item()) == P
+
+
 @pytest.mark.parametrize("tiles_x", [2048, 2049])
 def test_backward_tile_order_limit(tiles_x):
     # 2048 x 16 = 32768 tiles, the largest image whose backward launches its
