@@ -297,75 +297,121 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3(BwdArgs a)
     }
 }
 
+// Four consecutive elements of a row from element i, `rem` of them inside it.
+// Rows start at multiples of n: 16-byte accesses that are only 4-byte aligned.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t ushort4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float4v load4(const float* p, int rem)
+{
+    if (rem >= 4) return __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p));
+    float4v v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j < rem) v[j] = p[j];
+    return v;
+}
+
+template <typename V, typename T>
+__device__ __forceinline__ void store4(T* p, V v, int rem)
+{
+    if (rem >= 4) {
+        __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j < rem) p[j] = v[j];
+}
+
 // gs_render_bwd_adam for SH3: the backward above, with the Adam step applied
-// to every parameter element where its gradient is computed (culled Gaussians'
+// to every parameter element where its gradient is known (culled Gaussians'
 // and inactive bands' elements with a zero gradient, as the standalone step
 // steps them); a gradient array of `a` that is not NULL still receives the
-// gradient. The SH rows are stepped as soon as the colour gradient is known,
-// so that the coefficients are not kept past them.
-__global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3_adam(BwdArgs a, AdamFused f)
+// gradient.
+//
+// Bound by memory: 1,452 bytes per Gaussian in 118 read and 118 written rows.
+// With a Gaussian per lane throughout, a wave moved 256 bytes of a row at a time
+// and reached 4.5 TB/s (0.957 ms at 3M Gaussians). Here the workgroup's 256
+// Gaussians go through their 48 coefficient rows with four Gaussians per lane, a
+// KB per wave and access, wave w taking rows 12 w to 12 w + 11 (0.86 ms, 5.0
+// TB/s): it loads them into LDS, from where each lane takes its own Gaussian's
+// for the colour's clamp and direction gradient, and steps them once the lanes
+// have left the basis values and colour gradients there. Two workgroups per
+// compute unit; three spill (1.03 ms), and 3, 4 or 12 rows of moments in flight,
+// the first ones loaded before the geometry, or bands of Gaussians per XCD are
+// no faster.
+constexpr int kAdamRows = GS_SH_COEFFS / (kBlock / kWave);   // coefficient rows per wave
+constexpr int kAdamBatch = 6;                                // rows whose moments are in flight together
+
+__global__ __launch_bounds__(kBlock, 2) void k_preprocess_bwd_sh3_adam(BwdArgs a, AdamFused f)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.n) return;
-    const int64_t n = a.n;
-    const bool vis = a.tiles_touched[i] != 0;
+    static_assert(kBlock == 4 * kWave, "four Gaussians per lane");
+    __shared__ __align__(16) float rows[GS_SH_COEFFS][kBlock];   // coefficients
+    __shared__ __align__(16) float yg[16 + 3][kBlock];           // Y_0..15 and the colour gradient
+    const int t = threadIdx.x, wave = t >> 6, lane = __lane_id();
+    const int64_t n = a.n, i0 = (int64_t)blockIdx.x * kBlock;
+    const int i = (int)i0 + t;
+    const bool in = i < a.n;
+    const int64_t i4 = i0 + 4 * lane;
+    const int rem = (int)min((int64_t)4, n - i4);   // of this lane's four Gaussians
+    const int r0 = kAdamRows * wave;
+    {
+        float4v p[kAdamRows];
+#pragma unroll
+        for (int j = 0; j < kAdamRows; ++j) p[j] = load4(a.sh + (r0 + j) * n + i4, rem);
+#pragma unroll
+        for (int j = 0; j < kAdamRows; ++j) *reinterpret_cast<float4v*>(&rows[r0 + j][4 * lane]) = p[j];
+    }
+    constexpr int kT = 4;   // the SH tensor
+    float4v m[kAdamBatch], v[kAdamBatch];
+    auto load_moments = [&](int b0) {
+#pragma unroll
+        for (int j = 0; j < kAdamBatch; ++j) {
+            const int64_t e = (r0 + b0 + j) * n + i4;
+            m[j] = load4(f.m[kT] + e, rem);
+            v[j] = load4(f.v[kT] + e, rem);
+        }
+    };
+    const bool vis = in && a.tiles_touched[i] != 0;
+    float mu[3] = {}, ls[3] = {}, q[4] = {}, logit = 0.f;
+    if (in) {
+        for (int j = 0; j < 3; ++j) mu[j] = __builtin_nontemporal_load(&a.means[j * n + i]);
+        for (int j = 0; j < 3; ++j) ls[j] = __builtin_nontemporal_load(&a.log_scales[j * n + i]);
+        for (int j = 0; j < 4; ++j) q[j] = __builtin_nontemporal_load(&a.quats[j * n + i]);
+        logit = __builtin_nontemporal_load(&a.logits[i]);
+    }
+    float g9[kAccStride];
+    for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
+    if (vis) {
+        const float* ap = a.acc + (size_t)i * kAccStride;
+        for (int k = 0; k < kAccStride; ++k) g9[k] = __builtin_nontemporal_load(ap + k);
+    }
+    __syncthreads();
+
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
     gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
-    float g9[kAccStride];
-    for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
-    float Y[16], gc[3] = {0.f, 0.f, 0.f}, dY[16];
-    for (int k = 0; k < 16; ++k) Y[k] = dY[k] = 0.f;
+    float Y[16], gc[3] = {0.f, 0.f, 0.f};
+    for (int k = 0; k < 16; ++k) Y[k] = 0.f;
     const int nb = (a.sh_degree + 1) * (a.sh_degree + 1);
-    float mu[3], ls[3], q[4];
-    for (int j = 0; j < 3; ++j) mu[j] = __builtin_nontemporal_load(&a.means[j * n + i]);
-    for (int j = 0; j < 3; ++j) ls[j] = __builtin_nontemporal_load(&a.log_scales[j * n + i]);
-    for (int j = 0; j < 4; ++j) q[j] = __builtin_nontemporal_load(&a.quats[j * n + i]);
-    const float logit = __builtin_nontemporal_load(&a.logits[i]);
-    float coef[GS_SH_COEFFS];
-    for (int k = 0; k < GS_SH_COEFFS; ++k) coef[k] = 0.f;
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f, il = 0.f;
     if (vis) {
-        const float* ap = a.acc + (size_t)i * kAccStride;
-        for (int k = 0; k < kAccStride; ++k) g9[k] = __builtin_nontemporal_load(ap + k);
         geometry_bwd(a.cam, mu, ls, q, logit, g9, gg);
         const float vx = mu[0] - a.cam.campos[0], vy = mu[1] - a.cam.campos[1], vz = mu[2] - a.cam.campos[2];
         const float len = sqrtf(vx * vx + vy * vy + vz * vz);
-        il = 1.f / len;
-        d0 = vx * il;
-        d1 = vy * il;
-        d2 = vz * il;
+        const float il = 1.f / len;
+        const float d0 = vx * il, d1 = vy * il, d2 = vz * il;
         sh_basis16(d0, d1, d2, Y);
         if (a.sh_y0_folded) Y[0] = 1.f;
         float pre[3] = {0.5f, 0.5f, 0.5f};
         for (int k = 0; k < 16; ++k)
-            for (int c = 0; c < 3; ++c) {
-                coef[3 * k + c] = k < nb ? __builtin_nontemporal_load(a.sh + (3 * k + c) * n + i) : 0.f;
-                pre[c] += Y[k] * coef[3 * k + c];
-            }
+            for (int c = 0; c < 3; ++c) pre[c] += Y[k] * (k < nb ? rows[3 * k + c][t] : 0.f);
         for (int c = 0; c < 3; ++c) gc[c] = pre[c] > 0.f ? g9[6 + c] : 0.f;
-        for (int k = 0; k < 16; ++k) dY[k] = coef[3 * k] * gc[0] + coef[3 * k + 1] * gc[1] + coef[3 * k + 2] * gc[2];
-    }
-    // the SH rows, two bands (6 rows) per batch
-    constexpr int kShBatch = 6;
-#pragma unroll
-    for (int r0 = 0; r0 < GS_SH_COEFFS; r0 += kShBatch) {
-        int tb[kShBatch], rb[kShBatch];
-        float pb[kShBatch], gb[kShBatch];
-#pragma unroll
-        for (int j = 0; j < kShBatch; ++j) {
-            const int r = r0 + j, k = r / 3, c = r % 3;
-            tb[j] = 4;
-            rb[j] = r;
-            gb[j] = k < nb ? Y[k] * gc[c] : 0.f;
-            // coefficients the backward did not read are read here
-            pb[j] = vis && k < nb ? coef[r] : __builtin_nontemporal_load(a.sh + r * n + i);
-            if (a.dsh) __builtin_nontemporal_store(gb[j], a.dsh + r * n + i);
-        }
-        adam_apply(f, tb, rb, n, i, pb, gb);
-    }
-    if (vis) {
+        float dY[16];
+        for (int k = 0; k < 16; ++k)
+            dY[k] = k < nb ? rows[3 * k][t] * gc[0] + rows[3 * k + 1][t] * gc[1] + rows[3 * k + 2][t] * gc[2] : 0.f;
         float dd[3] = {0.f, 0.f, 0.f};
         sh_basis16_vjp(d0, d1, d2, dY, dd);
         // d = v / |v|: dv = (dd - d (d . dd)) / |v|
@@ -374,6 +420,46 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3_adam(BwdArgs a, A
         gg.dmu[1] += (dd[1] - d1 * dot) * il;
         gg.dmu[2] += (dd[2] - d2 * dot) * il;
     }
+    for (int k = 0; k < 16; ++k) yg[k][t] = Y[k];
+    for (int c = 0; c < 3; ++c) yg[16 + c][t] = gc[c];
+    __syncthreads();
+
+    float4v gc4[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) gc4[c] = *reinterpret_cast<const float4v*>(&yg[16 + c][4 * lane]);
+    if (rem > 0) {
+#pragma unroll
+        for (int b0 = 0; b0 < kAdamRows; b0 += kAdamBatch) {
+            load_moments(b0);
+#pragma unroll
+            for (int j = 0; j < kAdamBatch; ++j) {
+                const int r = r0 + b0 + j, k = r / 3, c = (b0 + j) % 3;   // r0 is a multiple of 3
+                const int64_t e = r * n + i4;
+                float4v g = {0.f, 0.f, 0.f, 0.f}, w = *reinterpret_cast<const float4v*>(&rows[r][4 * lane]);
+                if (k < nb) g = *reinterpret_cast<const float4v*>(&yg[k][4 * lane]) * gc4[c];
+                if (a.dsh) store4<float4u>(a.dsh + e, g, rem);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    float pu = w[u], mu_ = m[j][u], vu = v[j][u];
+                    adam_update(pu, mu_, vu, g[u], f.c.b1, f.c.omb1, f.c.b2[kT], f.c.omb2[kT], f.c.inv_sqrt_bc2[kT],
+                                f.c.eps, f.c.step_size[f.c.row0[kT] + r]);
+                    w[u] = pu;
+                    m[j][u] = mu_;
+                    v[j][u] = vu;
+                }
+                store4<float4u>(f.m[kT] + e, m[j], rem);
+                store4<float4u>(f.v[kT] + e, v[j], rem);
+                store4<float4u>(f.p[kT] + e, w, rem);
+                if (f.h[kT]) {
+                    ushort4u h;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) h[u] = __builtin_bit_cast(uint16_t, (_Float16)w[u]);
+                    store4<ushort4u>(f.h[kT] + e, h, rem);
+                }
+            }
+        }
+    }
+    if (!in) return;
     for (int j = 0; j < 3; ++j) {
         if (a.dmeans) __builtin_nontemporal_store(gg.dmu[j], &a.dmeans[j * n + i]);
         if (a.dlog_scales) __builtin_nontemporal_store(gg.dls[j], &a.dlog_scales[j * n + i]);

@@ -199,3 +199,54 @@ def test_adam_inside_the_backward(scene, sh_degree):
             assert torch.equal(u, w)
     say("  bit-exact against the backward then gs_adam_step (%d elements); without gradient outputs the "
         "same bits (%d parameters moved)" % (sum(g["rows"] * g["n"] for g in opt.groups), moved))
+
+
+@pytest.mark.parametrize("n,offset", [(1, 0), (3, 1), (255, 2), (257, 0), (258, 3), (1021, 1)])
+def test_adam_inside_the_backward_ragged(n, offset):
+    # counts that end inside a lane's four Gaussians or a workgroup, rows and
+    # arrays that are only 4-byte aligned, binary16 copies; nothing is written
+    # beyond any array
+    from paper_2609_05255_amd import inputs
+    from parity import tiny_camera
+    sc = inputs.make_scene("tiny").subset(np.arange(n))
+    cam = tiny_camera()
+    st = gs.SceneTensors(sc)
+    guard = 77.0
+
+    def place(t, dtype=torch.float32):   # a copy at `offset` elements into a larger buffer, guarded on both sides
+        big = torch.full((t.numel() + offset + 9,), guard, device="cuda", dtype=dtype)
+        view = big[offset + 4:offset + 4 + t.numel()].view(t.shape)
+        view.copy_(t)
+        return big, view
+    bufs = {}
+    for name in ("means", "log_scales", "quats", "opacity_logits", "sh"):
+        bufs[name], v = place(getattr(st, name))
+        setattr(st, name, v)
+    fr = gs.Frame(n, cam.width, cam.height, gs.GS_APP_SH3, 1 << 16)
+    fr.pre.color_jac = None
+    cs = gs.camera_struct(cam)
+    fr.forward(cs, st)
+    up = torch.from_numpy(inputs.make_upstream_grad(cam.width, cam.height, 2)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    groups, before = [], []
+    for name, rows in (("means", 3), ("log_scales", 3), ("quats", 4), ("opacity_logits", 1), ("sh", 48)):
+        p = getattr(st, name).view(rows, n)
+        g = dict(param=p, rows=rows, n=n, beta2=0.999, lr=[1e-3 * (r + 1) for r in range(rows)])
+        bufs["m" + name], g["exp_avg"] = place(torch.randn(rows, n, device="cuda", generator=gen) * 1e-3)
+        bufs["v" + name], g["exp_avg_sq"] = place(torch.rand(rows, n, device="cuda", generator=gen) * 1e-6)
+        bufs["h" + name], g["param_half"] = place(torch.zeros(rows, n, device="cuda"), torch.float16)
+        groups.append(g)
+        before.append({k: g[k].clone() for k in ("param", "exp_avg", "exp_avg_sq")})
+    gs.gs_render_bwd_adam(cs, st.gaussians(), st.appearance(gs.GS_APP_SH3), fr.pre, fr.values, fr.ranges, fr.final_T,
+                          fr.n_contrib, up, fr.grads, groups, 0.9, 1e-15, 5, fr.workspace, fr.ws_bytes)
+    torch.cuda.synchronize()
+    ref = [dict(b, rows=g["rows"], n=n, beta2=0.999, lr=g["lr"], grad=getattr(fr, k).view(-1)[:g["rows"] * n].clone())
+           for b, g, k in zip(before, groups, GRAD_NAMES)]
+    gs.gs_adam_step(ref, 0.9, 1e-15, 5)
+    torch.cuda.synchronize()
+    for g, r in zip(groups, ref):
+        for key in ("param", "exp_avg", "exp_avg_sq"):
+            assert torch.equal(g[key], r[key]), (g["rows"], key)
+        assert torch.equal(g["param_half"], r["param"].half())
+    for name, big in bufs.items():
+        assert bool((big[:offset + 4] == guard).all()) and bool((big[-5:] == guard).all()), name
