@@ -325,7 +325,7 @@ gs_status gs_render_work(const gs_camera* cam, const gs_preprocessed* pre, int64
  *   rounding.
  * workspace: at least gs_workspace_size(n, width, height, ...) bytes for this
  *   camera's image size (it holds the per-Gaussian accumulators and an order
- *   of the tiles: images of up to 32768 tiles are walked longest list walk
+ *   of the tiles: images of 257 to 32768 tiles are walked longest list walk
  *   first, which evens out the work per SIMD; the order does not change what
  *   is computed).
  */

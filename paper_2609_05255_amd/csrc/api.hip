@@ -541,7 +541,7 @@ gs_status render_bwd(const gs_camera* cam, const gs_gaussians* g, const gs_appea
         if (app->kind == GS_APP_NEURAL && grads->dmlp_w) GS_HIP(launch_clear(grads->dmlp_w, neural_weights(*app), s));
         return ok();
     }
-    const bool ordered = tile_order_supported(c);
+    const bool ordered = tile_order_wanted(c);
     timing_begin(GS_KERNEL_BWD_PREP, s);
     GS_HIP(launch_bwd_prep(c, tile_ranges, n_contrib, ws.acc, (int64_t)kAccStride * g->n, ws.walk_cls,
                            ordered ? ws.tile_order : nullptr, s));

@@ -68,8 +68,9 @@ constexpr int kRadix = 256;
 constexpr int kDupChunk = 1024;   // depth-ordered Gaussians per workgroup in entry emission
 constexpr int kBlockDim = 4;      // a block is kBlockDim x kBlockDim tiles
 // Tile order of the blend backward: classes of walk length (16 per octave of a
-// u32) and the largest image it is taken for (larger images keep the plain order).
+// u32) and the images it is taken for (others keep the plain order).
 constexpr int kWalkClasses = 512;
+constexpr int kMinOrderedTiles = 256;
 constexpr int kMaxOrderedTiles = 32768;
 
 // Workgroups of the decoder preprocess backward (grid-stride), one partial
@@ -180,7 +181,7 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
 hipError_t launch_clear(float* p, int64_t count, hipStream_t s);
 hipError_t launch_blend_count(const Cam& cam, const gs_splat* splats, const uint32_t* values,
                               const uint32_t* tile_ranges, uint64_t* counts, hipStream_t s);
-bool tile_order_supported(const Cam& cam);   // at most kMaxOrderedTiles tiles
+bool tile_order_wanted(const Cam& cam);
 // The backward's preparation: acc[0, acc_count) cleared and, when `order` is
 // given, the tiles' launch order, longest walk first (walk_cls: n_tiles scratch).
 hipError_t launch_bwd_prep(const Cam& cam, const uint32_t* tile_ranges, const uint32_t* n_contrib, float* acc,

@@ -157,10 +157,11 @@ def test_backward_tile_order_limit(tiles_x):
     check_all(sc, tiny_camera(16 * tiles_x, 256), label="wide-bwd-%d" % tiles_x)
 
 
-@pytest.mark.parametrize("tiles", [(48, 32), (29, 53), (64, 32), (3, 683), (64, 48), (7, 439)])
+@pytest.mark.parametrize("tiles", [(16, 16), (1, 257), (48, 32), (29, 53), (64, 32), (3, 683), (64, 48), (7, 439)])
 def test_pixels_per_lane_limits(tiles):
     # 1536, 2048 and 3072 tiles and the next sizes above them, where the blend
-    # kernels take more pixels per lane: clustered splats (long lists, a count
+    # kernels take more pixels per lane, and 256 tiles, above which the backward
+    # orders its tiles: clustered splats (long lists, a count
     # that is no multiple of the splats per step, saturated pixels) and a
     # background that stays in sight
     w, h = 16 * tiles[0] - 5, 16 * tiles[1] - 3
