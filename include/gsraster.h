@@ -272,6 +272,8 @@ gs_status gs_preprocess_noalloc(const gs_camera* cam, const gs_gaussians* g, con
  * Method: the Gaussians are sorted by depth; each gets one entry per 4x4-tile
  *   block its rectangle meets, in that order; a stable sort by block id groups
  *   them; each block's 16 tile lists are then written by ordered compaction.
+ *   With few Gaussians each block takes its entries from all of them instead,
+ *   in depth order. The lists are the same.
  */
 #define GS_PAIRS_ON_DEVICE UINT64_MAX
 gs_status gs_bin_sort(const gs_camera* cam, const gs_preprocessed* pre, int64_t n, uint64_t num_pairs,

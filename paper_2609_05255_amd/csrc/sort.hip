@@ -20,6 +20,9 @@
 // count do nothing, and their rows are not read. A single-pass block sort's
 // scatter has one workgroup more, which writes the tile lists' segment table
 // from that pass's digit totals (the blocks' entry counts).
+//
+// With few Gaussians one workgroup sorts them by depth in LDS, and each block
+// finds its own entries among all of them (k_small_depth_sort, k_small_lists).
 #include "gs_internal.h"
 
 namespace gsr {
@@ -1385,8 +1388,8 @@ hipError_t launch_tile_lists(const Cam& cam, PairCount pairs, uint64_t capacity,
 
 // Whether the tile lists come from small_lists: within its LDS, and where the
 // blocks' search of all Gaussians costs less than the launches it saves (up to
-// kSmallWork tests: 12,000 Gaussians in 510 blocks 32 us for the two launches,
-// 24,000 in 510 61, against 84 to 88 for the general path's).
+// kSmallWork tests: 12,000 Gaussians in 510 blocks 35 us for the two launches,
+// 24,000 in 510 70, against 84 to 88 for the general path's).
 bool small_lists(const Cam& cam, int64_t n)
 {
     return n <= kSmallMax && packed_rects(cam) && (int64_t)cam.tiles_x * cam.tiles_y <= kSmallTiles &&
