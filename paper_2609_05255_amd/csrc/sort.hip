@@ -22,7 +22,7 @@
 // from that pass's digit totals (the blocks' entry counts).
 //
 // With few Gaussians one workgroup sorts them by depth in LDS, and each block
-// finds its own entries among all of them (k_small_depth_sort, k_small_lists).
+// finds its own entries among all of them (k_small_depth_sort, k_small_counts, k_small_lists).
 #include "gs_internal.h"
 
 namespace gsr {
@@ -1015,7 +1015,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_emit(const uint32_t* __restrict
 // it where a workgroup's registers run out). Up to kSmallMax one workgroup per
 // 4x4-tile block then finds the block's entries among all Gaussians, twice: to
 // count its tile lists and to write them. Binning 1,024 Gaussians into 16 tiles
-// takes 28 us in three launches (103 before), 12,000 into 1,200 tiles 74 (136).
+// takes 28 us in three launches (103 before), 12,000 into 1,200 tiles 73 (136).
 // Both are for grids whose rectangles are packed.
 constexpr int kSmallSortItems = 12, kSmallItems = 24;             // keys per thread
 constexpr int64_t kSmallSort = (int64_t)kListThreads * kSmallSortItems;
@@ -1102,17 +1102,59 @@ __global__ __launch_bounds__(kListThreads) void k_small_depth_sort(const uint32_
     }
 }
 
+// One workgroup per block: the lengths of its 16 tile lists. Lengths need no
+// order, so nothing is compacted: each wave adds up ballots of its Gaussians'
+// masks in scalar registers (15 us for 20,001 Gaussians in 130 blocks, 22 with the lists
+// compacted first as below; 2.9 and 4.5 for 1,024 in one).
+__global__ __launch_bounds__(kListThreads) void k_small_counts(const uint2* __restrict__ order, int n, int blocks_x,
+                                                               int tiles_x, int tiles_y,
+                                                               uint32_t* __restrict__ tile_len)
+{
+    constexpr int kWaves = kListThreads / kWave, kTiles = kBlockDim * kBlockDim;
+    static_assert(kWaves == kTiles && kTiles <= kWave, "a wave per tile");
+    __shared__ uint32_t counts[kWaves][kTiles];
+    const int t = threadIdx.x, wave = t >> 6, lane = __lane_id();
+    const int bx = (int)blockIdx.x % blocks_x, by = (int)blockIdx.x / blocks_x;
+    uint32_t c[kTiles] = {};
+    for (int i0 = wave * kWave; i0 < n; i0 += 4 * kListThreads) {
+        uint2 r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kListThreads + lane;
+            r[u] = i < n ? unpack_rect32(order[i].y) : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t m = tile_mask(r[u], bx, by);
+            if (__ballot(m != 0) == 0) continue;
+#pragma unroll
+            for (int k = 0; k < kTiles; ++k) c[k] += (uint32_t)__popcll(__ballot((m >> k) & 1u));
+        }
+    }
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) mine = lane == k ? c[k] : mine;
+    if (lane < kTiles) counts[wave][lane] = mine;
+    __syncthreads();
+    const int tx = kBlockDim * bx + (t & 3), ty = kBlockDim * by + (t >> 2);
+    if (t >= kTiles || tx >= tiles_x || ty >= tiles_y) return;
+    uint32_t len = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) len += counts[w][t];
+    tile_len[ty * tiles_x + tx] = len;
+}
+
 // One workgroup per block, one wave per tile of it. The Gaussians that meet the
 // block are compacted, in depth order, into LDS (position and mask of the
-// block's tiles); each wave then counts those of its tile (kEmit false: into
-// tile_len) or writes them (kEmit true), at the sum of the lengths of the tiles
-// before, which every workgroup adds up for its own four rows of tiles. Pairs
-// over the capacity (the preprocess's count, or the lengths' sum) leave every
-// range empty.
-template <int kItems, bool kEmit>
+// block's tiles); each wave then writes those of its tile at the sum of the
+// lengths of the tiles before, which every workgroup adds up for its own four
+// rows of tiles. Pairs over the capacity (the preprocess's count, or the
+// lengths' sum) leave every range empty.
+template <int kItems>
 __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __restrict__ order, int n,
                                                               int blocks_x,
-                                                              int tiles_x, int tiles_y, uint32_t* __restrict__ tile_len,
+                                                              int tiles_x, int tiles_y,
+                                                              const uint32_t* __restrict__ tile_len,
                                                               PairCount pairs, uint64_t capacity,
                                                               uint32_t* __restrict__ values,
                                                               uint32_t* __restrict__ tile_ids,
@@ -1146,21 +1188,19 @@ __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __res
     }
     if (lane == 0) wcount[wave] = found;
     // lengths of the tiles before each row of this block's, and of all tiles
-    if (kEmit) {
-        uint64_t s[kBlockDim + 1] = {};
-        const int n_tiles = tiles_x * tiles_y;
-        for (int k = t; k < n_tiles; k += kListThreads) {
-            const uint32_t len = tile_len[k];
+    uint64_t s[kBlockDim + 1] = {};
+    const int n_tiles = tiles_x * tiles_y;
+    for (int k = t; k < n_tiles; k += kListThreads) {
+        const uint32_t len = tile_len[k];
 #pragma unroll
-            for (int r = 0; r < kBlockDim; ++r)
-                s[r] += k < (kBlockDim * by + r) * tiles_x + kBlockDim * bx ? len : 0u;
-            s[kBlockDim] += len;
-        }
+        for (int r = 0; r < kBlockDim; ++r)
+            s[r] += k < (kBlockDim * by + r) * tiles_x + kBlockDim * bx ? len : 0u;
+        s[kBlockDim] += len;
+    }
 #pragma unroll
-        for (int r = 0; r <= kBlockDim; ++r) {
-            for (int o = 32; o > 0; o >>= 1) s[r] += __shfl_xor(s[r], o);
-            if (lane == 0) sums[wave][r] = s[r];
-        }
+    for (int r = 0; r <= kBlockDim; ++r) {
+        for (int o = 32; o > 0; o >>= 1) s[r] += __shfl_xor(s[r], o);
+        if (lane == 0) sums[wave][r] = s[r];
     }
     __syncthreads();
     uint32_t at = 0, m_all = 0;
@@ -1180,39 +1220,30 @@ __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __res
     const int tx = kBlockDim * bx + (wave & 3), ty = kBlockDim * by + (wave >> 2);
     if (tx >= tiles_x || ty >= tiles_y) return;
     const int tile = ty * tiles_x + tx;
-    if (!kEmit) {
-        uint32_t c = 0;
-        for (uint32_t e0 = 0; e0 < m_all; e0 += kWave) {
-            const uint32_t e = e0 + lane;
-            c += (uint32_t)__popcll(__ballot(e < m_all && (list[e] >> (16 + wave)) & 1u));
-        }
-        if (lane == 0) tile_len[tile] = c;
-    } else {
-        uint64_t start = 0, total = 0;
+    uint64_t start = 0, total = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            start += sums[w][wave >> 2];
-            total += sums[w][kBlockDim];
+    for (int w = 0; w < kWaves; ++w) {
+        start += sums[w][wave >> 2];
+        total += sums[w][kBlockDim];
+    }
+    for (int k = 0; k < (wave & 3); ++k) start += tile_len[tile - (wave & 3) + k];
+    const bool over = pairs.overflow() || total > capacity;
+    uint32_t pos = (uint32_t)start;
+    for (uint32_t e0 = 0; e0 < m_all && !over; e0 += kWave) {
+        const uint32_t e = e0 + lane;
+        const uint32_t v = e < m_all ? list[e] : 0u;
+        const bool on = (v >> (16 + wave)) & 1u;
+        const uint64_t b = __ballot(on);
+        if (on) {
+            const uint32_t q = pos + (uint32_t)__popcll(b & lanemask_lt());
+            values[q] = order[v & 0xFFFFu].x;
+            if (tile_ids) tile_ids[q] = (uint32_t)tile;
         }
-        for (int k = 0; k < (wave & 3); ++k) start += tile_len[tile - (wave & 3) + k];
-        const bool over = pairs.overflow() || total > capacity;
-        uint32_t pos = (uint32_t)start;
-        for (uint32_t e0 = 0; e0 < m_all && !over; e0 += kWave) {
-            const uint32_t e = e0 + lane;
-            const uint32_t v = e < m_all ? list[e] : 0u;
-            const bool on = (v >> (16 + wave)) & 1u;
-            const uint64_t b = __ballot(on);
-            if (on) {
-                const uint32_t q = pos + (uint32_t)__popcll(b & lanemask_lt());
-                values[q] = order[v & 0xFFFFu].x;
-                if (tile_ids) tile_ids[q] = (uint32_t)tile;
-            }
-            pos += (uint32_t)__popcll(b);
-        }
-        if (lane == 0) {
-            tile_ranges[2 * tile] = over ? 0u : (uint32_t)start;
-            tile_ranges[2 * tile + 1] = over ? 0u : pos;
-        }
+        pos += (uint32_t)__popcll(b);
+    }
+    if (lane == 0) {
+        tile_ranges[2 * tile] = over ? 0u : (uint32_t)start;
+        tile_ranges[2 * tile + 1] = over ? 0u : pos;
     }
 }
 
@@ -1388,8 +1419,8 @@ hipError_t launch_tile_lists(const Cam& cam, PairCount pairs, uint64_t capacity,
 
 // Whether the tile lists come from small_lists: within its LDS, and where the
 // blocks' search of all Gaussians costs less than the launches it saves (up to
-// kSmallWork tests: 12,000 Gaussians in 510 blocks 35 us for the two launches,
-// 24,000 in 510 70, against 84 to 88 for the general path's).
+// kSmallWork tests: 12,000 Gaussians in 510 blocks 36 us for the two launches,
+// 24,000 in 510 63, against 84 to 88 for the general path's).
 bool small_lists(const Cam& cam, int64_t n)
 {
     return n <= kSmallMax && packed_rects(cam) && (int64_t)cam.tiles_x * cam.tiles_y <= kSmallTiles &&
@@ -1408,9 +1439,9 @@ static void small_tiles(const Cam& cam, int n, const uint2* order, PairCount pai
 {
     const int bx = blocks_x_of(cam);
     const dim3 blocks((unsigned)(bx * blocks_y_of(cam)));
-    hipLaunchKernelGGL((k_small_lists<kItems, false>), blocks, dim3(kListThreads), 0, s, order, n, bx, cam.tiles_x,
-                       cam.tiles_y, tile_len, pairs, capacity, values, tile_ids, tile_ranges);
-    hipLaunchKernelGGL((k_small_lists<kItems, true>), blocks, dim3(kListThreads), 0, s, order, n, bx, cam.tiles_x,
+    hipLaunchKernelGGL(k_small_counts, blocks, dim3(kListThreads), 0, s, order, n, bx, cam.tiles_x, cam.tiles_y,
+                       tile_len);
+    hipLaunchKernelGGL(k_small_lists<kItems>, blocks, dim3(kListThreads), 0, s, order, n, bx, cam.tiles_x,
                        cam.tiles_y, tile_len, pairs, capacity, values, tile_ids, tile_ranges);
 }
 
