@@ -96,13 +96,12 @@ struct GeoGrad {
     float dls[3];
     float dq[4];
     float dlogit;
-    float dmean2d[2];
 };
 
 // Derivative of the geometry part of the preprocess (everything except colour),
-// from the moments of dL/dpower in g9[0..5] (kAccStride): with the conic
-// (a, b, c), dL/dmean2d = (a m_x + b m_y, c m_y + b m_x), dL/d(a, b, c) =
-// -(m_xx / 2, m_xy, m_yy / 2), and o dL/do = m_0 (below the cap alpha = o G).
+// from the accumulator's g9[0..5] (kAccStride): (g9[1], g9[2]) is dL/dmean2d,
+// dL/d(a, b, c) of the conic is -(m_xx / 2, m_xy, m_yy / 2), and o dL/do = m_0
+// (below the cap alpha = o G).
 __device__ __forceinline__ void geometry_bwd(const Cam& c, const float mu[3], const float ls[3], const float qraw[4],
                                              float logit, const float* g9, GeoGrad& out)
 {
@@ -175,9 +174,7 @@ __device__ __forceinline__ void geometry_bwd(const Cam& c, const float mu[3], co
     if (cly) dt[2] += c.fy * (uy * itz) * itz2 * dj12;
     else { dt[1] += -c.fy * itz2 * dj12; dt[2] += 2.f * c.fy * t[1] * itz2 * itz * dj12; }
     // projected mean px = fx tx / tz + cx
-    const float dmx = qa * g9[1] + qb * g9[2], dmy = qc * g9[2] + qb * g9[1];
-    out.dmean2d[0] = dmx;
-    out.dmean2d[1] = dmy;
+    const float dmx = g9[1], dmy = g9[2];
     dt[0] += c.fx * itz * dmx;
     dt[1] += c.fy * itz * dmy;
     dt[2] += -(c.fx * t[0] * dmx + c.fy * t[1] * dmy) * itz2;
@@ -230,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3(BwdArgs a)
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
-    gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
+    gg.dlogit = 0.f;
     float g9[kAccStride];
     for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
     float Y[16], gc[3] = {0.f, 0.f, 0.f};
@@ -292,8 +289,8 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_sh3(BwdArgs a)
     for (int j = 0; j < 4; ++j) __builtin_nontemporal_store(gg.dq[j], &a.dquats[j * n + i]);
     __builtin_nontemporal_store(gg.dlogit, &a.dlogits[i]);
     if (a.dmean2d) {
-        __builtin_nontemporal_store(gg.dmean2d[0], &a.dmean2d[i]);
-        __builtin_nontemporal_store(gg.dmean2d[1], &a.dmean2d[n + i]);
+        __builtin_nontemporal_store(g9[1], &a.dmean2d[i]);
+        __builtin_nontemporal_store(g9[2], &a.dmean2d[n + i]);
     }
 }
 
@@ -393,7 +390,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_preprocess_bwd_sh3_adam(BwdArgs a
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
-    gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
+    gg.dlogit = 0.f;
     float Y[16], gc[3] = {0.f, 0.f, 0.f};
     for (int k = 0; k < 16; ++k) Y[k] = 0.f;
     const int nb = (a.sh_degree + 1) * (a.sh_degree + 1);
@@ -475,8 +472,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_preprocess_bwd_sh3_adam(BwdArgs a
                             gg.dq[0], gg.dq[1], gg.dq[2], gg.dq[3], gg.dlogit};
     adam_apply(f, tg, rg, n, i, pg, gg11);
     if (a.dmean2d) {
-        __builtin_nontemporal_store(gg.dmean2d[0], &a.dmean2d[i]);
-        __builtin_nontemporal_store(gg.dmean2d[1], &a.dmean2d[n + i]);
+        __builtin_nontemporal_store(g9[1], &a.dmean2d[i]);
+        __builtin_nontemporal_store(g9[2], &a.dmean2d[n + i]);
     }
 }
 
@@ -496,7 +493,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_lobe(BwdArgs a)
     GeoGrad gg;
     for (int j = 0; j < 3; ++j) { gg.dmu[j] = 0.f; gg.dls[j] = 0.f; }
     for (int j = 0; j < 4; ++j) gg.dq[j] = 0.f;
-    gg.dlogit = gg.dmean2d[0] = gg.dmean2d[1] = 0.f;
+    gg.dlogit = 0.f;
     float g9[kAccStride];
     for (int k = 0; k < kAccStride; ++k) g9[k] = 0.f;
     float gc[3] = {0.f, 0.f, 0.f}, dl[kRows];
@@ -547,8 +544,8 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd_lobe(BwdArgs a)
     for (int j = 0; j < 4; ++j) __builtin_nontemporal_store(gg.dq[j], &a.dquats[j * n + i]);
     __builtin_nontemporal_store(gg.dlogit, &a.dlogits[i]);
     if (a.dmean2d) {
-        __builtin_nontemporal_store(gg.dmean2d[0], &a.dmean2d[i]);
-        __builtin_nontemporal_store(gg.dmean2d[1], &a.dmean2d[n + i]);
+        __builtin_nontemporal_store(g9[1], &a.dmean2d[i]);
+        __builtin_nontemporal_store(g9[2], &a.dmean2d[n + i]);
     }
 }
 
@@ -655,7 +652,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_preprocess_bwd_latent(BwdArgs a)
             for (int j = 0; j < 3; ++j) { a.dmeans[j * n + i] = gg.dmu[j]; a.dlog_scales[j * n + i] = gg.dls[j]; }
             for (int j = 0; j < 4; ++j) a.dquats[j * n + i] = gg.dq[j];
             a.dlogits[i] = gg.dlogit;
-            if (a.dmean2d) { a.dmean2d[i] = gg.dmean2d[0]; a.dmean2d[n + i] = gg.dmean2d[1]; }
+            if (a.dmean2d) { a.dmean2d[i] = g9[1]; a.dmean2d[n + i] = g9[2]; }
         }
         wave_lds_sync();   // st.dd is read before the next chunk restages
     }
@@ -823,7 +820,7 @@ __global__ __launch_bounds__(kBlock, kW == 32 ? 2 : 3) void k_preprocess_bwd_neu
             for (int j = 0; j < 3; ++j) { a.dmeans[j * n + i] = gg.dmu[j]; a.dlog_scales[j * n + i] = gg.dls[j]; }
             for (int j = 0; j < 4; ++j) a.dquats[j * n + i] = gg.dq[j];
             a.dlogits[i] = gg.dlogit;
-            if (a.dmean2d) { a.dmean2d[i] = gg.dmean2d[0]; a.dmean2d[n + i] = gg.dmean2d[1]; }
+            if (a.dmean2d) { a.dmean2d[i] = g9[1]; a.dmean2d[n + i] = g9[2]; }
         }
         if (resid) wave_lds_sync();   // the stage is read before the next chunk restages
     }

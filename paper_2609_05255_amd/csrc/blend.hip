@@ -85,6 +85,29 @@ __device__ __forceinline__ Staged staged(const float4& w0, const float4& w1, con
     return Staged{w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y};
 }
 
+// The backward needs the record's conic (a, b, c) as well, for the gradient of
+// the mean: a in the place of ka (one product per visit gives ka, the same bits
+// as the forward's), b and c in the third plane's spare words.
+struct StagedBwd : Staged {
+    float ca, cb, cc;
+};
+
+__device__ __forceinline__ void stage_words_bwd(const float4& c0, const float4& c1, const float4& c2, float4& w0,
+                                                float4& w1, float4& w2)
+{
+    float2 tail;
+    stage_words(c0, c1, c2, w0, w1, tail);
+    w0.z = c0.z;
+    w2 = make_float4(tail.x, tail.y, c0.w, c1.x);
+}
+
+__device__ __forceinline__ StagedBwd staged_bwd(const float4& w0, const float4& w1, const float4& w2)
+{
+    StagedBwd s{staged(w0, w1, make_float2(w2.x, w2.y)), w0.z, w2.z, w2.w};
+    s.ka = (0.5f * kLog2e) * w0.z;
+    return s;
+}
+
 // A wave's staged batch: three planes at one 16-byte stride, so that a splat's
 // reads share one address register.
 struct StageSlot {
@@ -136,27 +159,43 @@ __device__ __forceinline__ float merge16(float a, float b)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Wave sums of one splat's nine accumulator entries (kAccStride) from its six
-// per-lane sums over the lane's pixels: p0, p1, p2 (dL/dpower times 1, dy, dy^2)
-// and the colour gradient c. dx is the same in the four lanes of a column, so
-// the four rows of 16 lanes are added first, two values merged per lane swap,
-// and the moments in dx are products of the column sums. Within the rows, DPP
-// sums take two registers (8 lanes each) and a third (every other quad) at
-// once. The sum of entry e ends in lane reduce_src_lane(e); one LDS permute
-// brings the nine into the first lanes, so that their atomics stay one request
-// per 64 bytes (from four rows they are four, which at 3M Gaussians costs
-// 0.09 ms). 23 vector instructions, where a butterfly of selects and permutes
-// over nine values took 46. Every lane of the wave must call it (a disabled
-// DPP source lane reads 0).
-__device__ __forceinline__ float wave_reduce9(float p0, float p1, float p2, float c0, float c1, float c2, float dx,
-                                              bool odd_row, bool hi8, bool odd4, int src_byte)
+// dL/dmean of one splat over a lane's pixels, from their sums p0 and p1 of
+// dL/dpower times 1 and dy (they share dx): (a dx p0 + b p1, c p1 + b dx p0).
+// For long thin splats the two terms cancel by up to the conic's condition
+// number, so they are combined here, where they are small: from the finished
+// sums over all pixels (kept raw and combined once per Gaussian) the gradient's
+// error was 3 to 10 times larger (5e-6 to 9e-6 of it against 0.8e-6 to 2e-6 for
+// splats of sigma 40 x 4 pixels under a smooth upstream gradient, 4e-3 to 7e-3
+// against 1e-3 to 2e-3 at 300 x 0.1), and it took a conic other than the blended
+// record's. 6 vector instructions per visit with the staging above, 4% of the
+// backward's time at 3M Gaussians.
+__device__ __forceinline__ void mean_terms(const StagedBwd& s, float dx, float p0, float p1, float& gx, float& gy)
+{
+    const float m_x = dx * p0;
+    gx = __fmaf_rn(s.ca, m_x, s.cb * p1);
+    gy = __fmaf_rn(s.cc, p1, s.cb * m_x);
+}
+
+// Wave sums of one splat's nine accumulator entries (kAccStride) from its eight
+// per-lane sums over the lane's pixels: p0, p1, p2 (dL/dpower times 1, dy, dy^2),
+// the mean's gradient (gx, gy) and the colour's c. dx is the same in the four
+// lanes of a column, so the four rows of 16 lanes are added first, two values
+// merged per lane swap, and the other moments in dx are products of the column
+// sums. Within the rows, DPP sums take two registers (8 lanes each) and a third
+// (every other quad) at once. The sum of entry e ends in lane
+// reduce_src_lane(e); one LDS permute brings the nine into the first lanes, so
+// that their atomics stay one request per 64 bytes (from four rows they are
+// four, which at 3M Gaussians costs 0.09 ms). About 25 vector instructions, where a
+// butterfly of selects and permutes over nine values took 46. Every lane of the
+// wave must call it (a disabled DPP source lane reads 0).
+__device__ __forceinline__ float wave_reduce9(float p0, float p1, float p2, float gx, float gy, float c0, float c1,
+                                              float c2, float dx, bool upper, bool hi8, bool odd4, int src_byte)
 {
     const float s1 = merge16(merge32(p0, p1), merge32(c0, c1));   // rows: p0, c0, p1, c1
-    const float pc = merge32(p2, c2);
-    const float r1 = merge16(pc, pc);                             // rows: p2, p2, c2, c2
+    const float s2 = merge16(merge32(gx, gy), merge32(p2, c2));   // rows: gx, p2, gy, c2
     const float dx1 = dx * s1;
-    const float s2 = odd_row ? r1 : dx1;                          // rows: p0 dx, p2, p1 dx, c2
-    const float s3 = dx * dx1;                                    // row 0: p0 dx^2
+    const float dx2 = dx * dx1;
+    const float s3 = upper ? dx1 : dx2;                           // row 0: p0 dx^2, row 2: p1 dx
     const float h1 = s1 + dpp_f32<0x128>(s1), h2 = s2 + dpp_f32<0x128>(s2), h3 = s3 + dpp_f32<0x128>(s3);   // row_ror:8
     const float h = hi8 ? h2 : h1;
     // both sums before the select: a select over the sums' own code would become
@@ -178,10 +217,10 @@ __device__ __forceinline__ void add_scalar_row(float* row, int lane, float v)
     __hip_atomic_fetch_add(p + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The lane whose sum is entry e: M0, Mx, My, Mxx, Mxy, Myy, c0, c1, c2.
+// The lane whose sum is entry e: M0, mean x, mean y, Mxx, Mxy, Myy, c0, c1, c2.
 __device__ __forceinline__ int reduce_src_lane(int e)
 {
-    constexpr int src[kAccStride] = {0, 8, 32, 4, 40, 24, 16, 48, 56};
+    constexpr int src[kAccStride] = {0, 8, 40, 4, 36, 24, 16, 48, 56};
     int r = 0;
 #pragma unroll
     for (int k = 0; k < kAccStride; ++k) r = e == k ? src[k] : r;
@@ -402,13 +441,13 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
 // set of float atomics per (wave, splat).
 //
 // Bound by vector instruction issue: on the 3M-Gaussian 1600x1064 scene it takes
-// 0.271 ms, of which its instructions alone (149M wave instructions at 4 cycles;
-// the two transcendentals per pixel take 16) fill 0.24 ms or more. What shortened it
-// (from 0.318 ms and 204M): raw moments summed per splat and combined once per
-// Gaussian later, no opacity sum (dL/dopacity follows from the first moment),
+// 0.283 ms, of which its instructions alone (156M wave instructions at 4 cycles;
+// the two transcendentals per pixel take 16) fill 0.25 ms or more. What shortened it
+// (from 0.318 ms and 204M): second moments summed raw and their factors applied once
+// per Gaussian later, no opacity sum (dL/dopacity follows from the zeroth moment),
 // the recursion in A (no division beside T's), the alpha test on logarithms,
 // constants taken by the staging lane, lane masks combined as scalars, scalar
-// atomic addresses, and half the instructions of the reduction.
+// atomic addresses, and fewer instructions in the reduction.
 
 template <int kPix>
 __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, const gs_splat* __restrict__ splats,
@@ -473,7 +512,7 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
     __shared__ StageSlot stage[kTile * kTile / kPix / kWave];
     StageSlot& st = stage[wave];
     // lane roles of the reduction (wave_reduce9); lanes 0..8 add one entry each
-    const bool red_row = lane & 16, red_hi8 = lane & 8, red_odd4 = lane & 4;
+    const bool red_up = lane & 32, red_hi8 = lane & 8, red_odd4 = lane & 4;
     const int red_src = 4 * reduce_src_lane(lane);
     float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0, c2 = c0;
     uint32_t cid = 0, nid = 0;   // nid: the list entry of the batch after the prefetched one, loaded a batch early
@@ -488,7 +527,7 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
     }
     for (int bi = nbatch - 1; bi >= 0; --bi) {
         const uint32_t b = (uint32_t)bi * kWave;
-        stage_words(c0, c1, c2, st.w[0][lane], st.w[1][lane], st.tail(lane));
+        stage_words_bwd(c0, c1, c2, st.w[0][lane], st.w[1][lane], st.w[2][lane]);
         const uint32_t batch_id = cid;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -514,7 +553,7 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
             // lane that a splat does not reach takes its values by selects (a
             // product with zero would pass on an infinite colour or gradient).
             while (todo != 0) {
-                Staged s[kBwdGroup];
+                StagedBwd s[kBwdGroup];
                 float dx[kBwdGroup], dy[kBwdGroup], oG[kBwdGroup], alpha[kBwdGroup], inv[kBwdGroup];
                 uint64_t in[kBwdGroup];
                 int js[kBwdGroup];
@@ -524,7 +563,7 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
                     const uint64_t some = todo != 0 ? ~0ull : 0ull;   // none left: the last one again, masked out
                     j = todo != 0 ? 63 - (int)__builtin_clzll(todo) : j;
                     todo &= ~(1ull << j);
-                    s[g] = staged(st.w[0][j], st.w[1][j], st.tail(j));
+                    s[g] = staged_bwd(st.w[0][j], st.w[1][j], st.w[2][j]);
                     js[g] = j;
                     in[g] = some;
                 }
@@ -555,9 +594,12 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
                 }
                 float t[kBwdGroup];
 #pragma unroll
-                for (int g = 0; g < kBwdGroup; ++g)
-                    t[g] = wave_reduce9(p0[g], p1[g], p2[g], ac0[g], ac1[g], ac2[g], dx[g], red_row, red_hi8, red_odd4,
-                                        red_src);
+                for (int g = 0; g < kBwdGroup; ++g) {
+                    float gx, gy;
+                    mean_terms(s[g], dx[g], p0[g], p1[g], gx, gy);
+                    t[g] = wave_reduce9(p0[g], p1[g], p2[g], gx, gy, ac0[g], ac1[g], ac2[g], dx[g], red_up, red_hi8,
+                                        red_odd4, red_src);
+                }
 #pragma unroll
                 for (int g = 0; g < kBwdGroup; ++g) {
                     if (in[g] == 0) continue;
@@ -570,7 +612,7 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
                 const int j = 63 - (int)__builtin_clzll(todo);
                 todo ^= 1ull << j;
                 const uint32_t pos = b + (uint32_t)j;
-                const Staged s = staged(st.w[0][j], st.w[1][j], st.tail(j));
+                const StagedBwd s = staged_bwd(st.w[0][j], st.w[1][j], st.w[2][j]);
                 const float dx = px - s.mx;
                 const Quad q = column_quad(s, dx);
                 // per-lane sums over its pixels: colour gradient and dL/dpower times
@@ -607,7 +649,10 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
                     p2 = __fmaf_rn(pdy, dy, p2);
                 }
                 if (any == 0) continue;
-                const float t = wave_reduce9(p0, p1, p2, a_c0, a_c1, a_c2, dx, red_row, red_hi8, red_odd4, red_src);
+                float gx, gy;
+                mean_terms(s, dx, p0, p1, gx, gy);
+                const float t = wave_reduce9(p0, p1, p2, gx, gy, a_c0, a_c1, a_c2, dx, red_up, red_hi8, red_odd4,
+                                             red_src);
                 const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, j);
                 if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t);
             }

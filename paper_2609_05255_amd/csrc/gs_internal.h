@@ -51,11 +51,10 @@ static_assert(offsetof(gs_splat, power_min) == 36 && offsetof(gs_splat, depth) =
 
 // Per-Gaussian accumulator written by the blend backward, 9 floats: with dP =
 // dL/dpower of an uncapped pixel and (dx, dy) its centre minus the projected
-// mean, the sums over the pixels of dP, dP dx, dP dy, dP dx^2, dP dx dy,
-// dP dy^2, then dL/dcolour. Power = -(a dx^2 + c dy^2)/2 - b dx dy, so the
-// conic, mean and opacity gradients are linear in these sums with factors that
-// are the Gaussian's own (geometry_bwd): the preprocess backward
-// applies them once per Gaussian.
+// mean, the sums over the pixels of dP, the mean's gradient dP (a dx + b dy) and
+// dP (c dy + b dx), dP dx^2, dP dx dy, dP dy^2, then dL/dcolour. Power =
+// -(a dx^2 + c dy^2)/2 - b dx dy, so the gradients of the conic and the opacity are
+// these sums times factors that are the Gaussian's own (geometry_bwd).
 constexpr int kAccStride = 9;
 
 // Radix-sort geometry: workgroups of 1,024 threads, 4 to 12 keys per thread and

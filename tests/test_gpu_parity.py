@@ -171,6 +171,62 @@ def test_pixels_per_lane_limits(tiles):
     check_all(sc, tiny_camera(w, h, bg=(0.2, 0.4, 0.1)), label="pix-%dx%d" % tiles)
 
 
+def thin_scene(n, cam, long_px, short_px, seed=5):
+    """n splats of about long_px x short_px pixels (sigma), at every angle in the image plane, in the middle of the view."""
+    sc = inputs.make_scene("tiny", n=n)
+    r = np.random.default_rng(seed)
+    sc.means[0], sc.means[1], sc.means[2] = (r.uniform(-b, b, n) for b in (0.8, 0.5, 0.01))
+    sc.log_scales[0], sc.log_scales[1:] = np.log(3.0 * long_px / cam.fx), np.log(3.0 * short_px / cam.fx)
+    half = r.uniform(0, np.pi, n) / 2
+    sc.quats[:] = 0
+    sc.quats[0], sc.quats[3] = np.cos(half), np.sin(half)
+    sc.opacity_logits[:] = r.uniform(-2.5, -0.5, n)
+    return sc
+
+
+def smooth_upstream(cam, seed=3):
+    """An upstream gradient that varies slowly over the image, as a loss's does (white noise averages out in the sums
+    over a splat's pixels, and with it the cancellation between them)."""
+    r = np.random.default_rng(seed)
+    y, x = np.mgrid[0:cam.height, 0:cam.width]
+    wave = [np.sin(2 * np.pi * (r.uniform(0.5, 2) * x / cam.width + r.uniform(0.5, 2) * y / cam.height) +
+                   r.uniform(0, 6)) for _ in range(3)]
+    return (1e-3 * (1 + 0.5 * np.stack(wave))).astype(np.float32)
+
+
+@pytest.mark.parametrize("long_px,short_px,size", [
+    (10, 1, (480, 320)), (10, 1, (800, 608)), (10, 1, (1600, 1064)),
+    (40, 4, (480, 320)), (40, 4, (800, 608)), (40, 4, (1600, 1064)),
+    (60, 0.5, (480, 320)), (60, 0.5, (800, 608)), (60, 0.5, (1600, 1064)),
+    (300, 0.1, (480, 320)), (300, 0.1, (800, 608))])
+def test_mean_gradient_of_long_thin_splats(long_px, short_px, size):
+    # dL/dmean2d of a long thin splat is a difference of terms up to the conic's
+    # condition number larger, with the conic of the record that was blended. The
+    # three sizes take the three numbers of pixels per lane. The measure is the
+    # error that fp32 leaves in any case: the oracle with each pixel's power and
+    # alpha in fp32, its products and sums in fp64. Products rounded where the terms
+    # are small add at most about as much again, independently of it: together
+    # sqrt(2) times, 1.5 with the medians' spread. The additions of the waves' sums
+    # round to 2^-24 of the running sum, which is up to 16 times the result (the
+    # splat's two sides of its mean cancel): 1e-6 more. Combined from the finished
+    # sums the errors were 3e-6 to 7e-6 at 40 x 4, 2e-5 at 10 x 1 in the largest image.
+    cam = tiny_camera(*size)
+    sc = thin_scene(160, cam, long_px, short_px)
+    pre = orc.preprocess(cam, sc)
+    values, _, ranges = orc.bin_sort(cam, pre)
+    margin = orc.render_fwd(cam, pre, ranges, values)[3]
+    g = (smooth_upstream(cam) * (margin > 1.0)[None]).astype(np.float32)
+    ref = orc.render_bwd(cam, sc, pre, ranges, values, g, mode="f64")["dmean2d"]
+    fp32 = orc.render_bwd(cam, sc, pre, ranges, values, g, mode="f32")["dmean2d"]
+    gpu = run_gpu(sc, cam, "sh3", 3, g, capacity=values.size)["grads"]["dmean2d"]
+
+    def error(d):
+        return np.median(np.linalg.norm(d - ref, axis=0) / np.linalg.norm(ref, axis=0))
+    say("case thin %g x %g px, %dx%d: dmean2d error %.2e, in fp32 in any case %.2e" % (long_px, short_px, *size,
+                                                                                      error(gpu), error(fp32)))
+    assert error(gpu) <= 1.5 * error(fp32) + 1e-6
+
+
 @pytest.mark.parametrize("degree", [3, 1])
 def test_sh3_backward_without_the_colour_jacobian(degree):
     # gs_preprocessed.color_jac NULL: the preprocess writes no view-direction
