@@ -1014,9 +1014,11 @@ __global__ __launch_bounds__(kBlock) void k_tile_emit(const uint32_t* __restrict
 // us at 1,024, 46 at 12,000; the passes above take 57 and 69 there, and overtake
 // it where a workgroup's registers run out). Up to kSmallMax one workgroup per
 // 4x4-tile block then finds the block's entries among all Gaussians, twice: to
-// count its tile lists and to write them. Binning 1,024 Gaussians into 16 tiles
-// takes 28 us in three launches (103 before), 12,000 into 1,200 tiles 73 (136).
-// Both are for grids whose rectangles are packed.
+// count its tile lists and to write them. Both are for grids whose rectangles are
+// packed. The whole binning, this way / with the depth order and the block
+// entries of the path above (us; lists of a few and of all Gaussians): 4,096
+// Gaussians in 16 tiles 37 / 53, in 1,200 tiles 33 / 64 and 41 / 153; 12,288 in
+// 16 tiles 82 to 84 / 80, in 1,200 tiles 67 / 90 and 94 / 191.
 constexpr int kSmallSortItems = 12, kSmallItems = 24;             // keys per thread
 constexpr int64_t kSmallSort = (int64_t)kListThreads * kSmallSortItems;
 constexpr int64_t kSmallMax = (int64_t)kListThreads * kSmallItems;
@@ -1145,10 +1147,10 @@ __global__ __launch_bounds__(kListThreads) void k_small_counts(const uint2* __re
 }
 
 // One workgroup per block, one wave per tile of it. The Gaussians that meet the
-// block are compacted, in depth order, into LDS (position and mask of the
-// block's tiles); each wave then writes those of its tile at the sum of the
-// lengths of the tiles before, which every workgroup adds up for its own four
-// rows of tiles. Pairs over the capacity (the preprocess's count, or the
+// block are compacted, in depth order, into LDS (index and mask of the block's
+// tiles; indices are below kSmallMax, so both share a word); each wave then
+// writes those of its tile at the sum of the lengths of the tiles before, which
+// every workgroup adds up for its own four rows of tiles. Pairs over the capacity (the preprocess's count, or the
 // lengths' sum) leave every range empty.
 template <int kItems>
 __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __restrict__ order, int n,
@@ -1161,7 +1163,9 @@ __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __res
                                                               uint32_t* __restrict__ tile_ranges)
 {
     constexpr int kWaves = kListThreads / kWave, kSlice = kWave * kItems;
+    constexpr int kFly = 4;   // rounds whose loads are in flight together
     static_assert(kWaves == kBlockDim * kBlockDim, "a wave per tile");
+    static_assert(kSmallMax <= 1 << 16, "index and mask share a word");
     __shared__ uint16_t smask[kListThreads * kItems];
     __shared__ uint32_t list[kListThreads * kItems];
     __shared__ uint32_t wcount[kWaves];
@@ -1209,12 +1213,21 @@ __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __res
         at += w < wave ? wcount[w] : 0u;
         m_all += wcount[w];
     }
-    for (int i0 = w0; i0 < w1; i0 += kWave) {
-        const int i = i0 + lane;
-        const uint32_t m = i < w1 ? smask[i] : 0u;
-        const uint64_t b = __ballot(m != 0);
-        if (m != 0) list[at + (uint32_t)__popcll(b & lanemask_lt())] = (uint32_t)i | (m << 16);
-        at += (uint32_t)__popcll(b);
+    for (int i0 = w0; i0 < w1; i0 += kFly * kWave) {
+        uint32_t gid[kFly];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const int i = i0 + u * kWave + lane;
+            gid[u] = i < w1 ? order[i].x : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const int i = i0 + u * kWave + lane;
+            const uint32_t m = i < w1 ? smask[i] : 0u;
+            const uint64_t b = __ballot(m != 0);
+            if (m != 0) list[at + (uint32_t)__popcll(b & lanemask_lt())] = gid[u] | (m << 16);
+            at += (uint32_t)__popcll(b);
+        }
     }
     __syncthreads();
     const int tx = kBlockDim * bx + (wave & 3), ty = kBlockDim * by + (wave >> 2);
@@ -1229,17 +1242,24 @@ __global__ __launch_bounds__(kListThreads) void k_small_lists(const uint2* __res
     for (int k = 0; k < (wave & 3); ++k) start += tile_len[tile - (wave & 3) + k];
     const bool over = pairs.overflow() || total > capacity;
     uint32_t pos = (uint32_t)start;
-    for (uint32_t e0 = 0; e0 < m_all && !over; e0 += kWave) {
-        const uint32_t e = e0 + lane;
-        const uint32_t v = e < m_all ? list[e] : 0u;
-        const bool on = (v >> (16 + wave)) & 1u;
-        const uint64_t b = __ballot(on);
-        if (on) {
-            const uint32_t q = pos + (uint32_t)__popcll(b & lanemask_lt());
-            values[q] = order[v & 0xFFFFu].x;
-            if (tile_ids) tile_ids[q] = (uint32_t)tile;
+    for (uint32_t e0 = 0; e0 < m_all && !over; e0 += kFly * kWave) {
+        uint32_t v[kFly];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const uint32_t e = e0 + u * kWave + lane;
+            v[u] = e < m_all ? list[e] : 0u;
         }
-        pos += (uint32_t)__popcll(b);
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+            const bool on = (v[u] >> (16 + wave)) & 1u;
+            const uint64_t b = __ballot(on);
+            if (on) {
+                const uint32_t q = pos + (uint32_t)__popcll(b & lanemask_lt());
+                values[q] = v[u] & 0xFFFFu;
+                if (tile_ids) tile_ids[q] = (uint32_t)tile;
+            }
+            pos += (uint32_t)__popcll(b);
+        }
     }
     if (lane == 0) {
         tile_ranges[2 * tile] = over ? 0u : (uint32_t)start;
@@ -1419,12 +1439,17 @@ hipError_t launch_tile_lists(const Cam& cam, PairCount pairs, uint64_t capacity,
 
 // Whether the tile lists come from small_lists: within its LDS, and where the
 // blocks' search of all Gaussians costs less than the launches it saves (up to
-// kSmallWork tests: 12,000 Gaussians in 510 blocks 36 us for the two launches,
-// 24,000 in 510 63, against 84 to 88 for the general path's).
+// kSmallWork tests). Each workgroup compacts every Gaussian that it finds, so with
+// more than kSmallSort of them there has to be work for many: a block for every
+// kListThreads Gaussians (the whole binning this way / with block entries, us, lists
+// of a few and of all Gaussians: 16,384 in 1 block 97 to 99 / 79 to 81, in 12
+// 81 and 99 / 87 and 101, in 35 79 and 101 / 92 and 132; 24,576 in 1 block 118 to 121 / 80 to 82,
+// in 12 94 and 121 / 90 and 105, in 35 88 and 122 / 93 and 136).
 bool small_lists(const Cam& cam, int64_t n)
 {
+    const int64_t blocks = (int64_t)blocks_x_of(cam) * blocks_y_of(cam);
     return n <= kSmallMax && packed_rects(cam) && (int64_t)cam.tiles_x * cam.tiles_y <= kSmallTiles &&
-           n * blocks_x_of(cam) * blocks_y_of(cam) <= kSmallWork;
+           n * blocks <= kSmallWork && (n <= kSmallSort || n <= blocks * kListThreads);
 }
 
 template <int kItems>

@@ -148,6 +148,23 @@ def test_few_gaussians_binning(n, size):
             assert not got.any() and int(fr.num_pairs.item()) == P
 
 
+@pytest.mark.parametrize("n,size", [(1, (64, 64)), (65, (50, 40)), (257, (16, 16)), (1025, (64, 64)), (4097, (70, 64)),
+                                    (12288, (64, 64)), (12289, (64, 64)), (12289, (768, 64)), (12289, (832, 64)),
+                                    (24576, (384, 256)), (24576, (64, 1536))])
+def test_few_gaussians_whole_image(n, size):
+    # every Gaussian in every tile: lists of all Gaussians out of one block, of
+    # 2 x 2 blocks with tiles outside the image, and of the fewest blocks (one for
+    # every 1,024 Gaussians) that more than 12,288 Gaussians are searched in
+    sc = inputs.make_scene("tiny", n=n)
+    sc.means[:] *= np.float32(0.2)
+    cam = tiny_camera(*size)
+    sc.log_scales[:] = np.float32(np.log(3.0 * max(size) / cam.fx))
+    gpu = run_gpu(sc, cam, capacity=n * -(-size[0] // 16) * -(-size[1] // 16))
+    values, tiles, ranges = orc.bin_sort(cam, orc.preprocess(cam, sc))
+    assert values.size == n * len(ranges)
+    compare_lists(gpu, values, tiles, ranges)
+
+
 @pytest.mark.parametrize("tiles_x", [2048, 2049])
 def test_backward_tile_order_limit(tiles_x):
     # 2048 x 16 = 32768 tiles, the largest image whose backward launches its
