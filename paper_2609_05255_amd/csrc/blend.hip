@@ -29,12 +29,17 @@ constexpr int kXcds = 8;
 // tiles. Few tiles leave the SIMDs (1,024) short of waves, and the kernel lasts
 // as long as its longest walk: more waves per tile shorten each, at the price of
 // each splat's set-up and reduction once per wave. The lines lie where both
-// sides measure equal (us, 1 / 2 / 4 pixels per lane):
-//   backward:  64 tiles 75 / 118 / 197, 600 tiles 90 / 122 / 209,
-//              1200 tiles 90 / 105 / 170, 1900 tiles 130 / 127 / 175,
-//              2560 tiles 155 / 145 / 161, 3200 tiles 207 / 194 / 193
-//   forward:   64 tiles 43 / 75, 600 tiles 62 / 89, 1200 tiles 62 / 76,
-//              1900 tiles 87 / 90, 2560 tiles 91 / 92, 3200 tiles 121 / 115
+// sides measure equal over lists of small and of large splats (the whole backward,
+// us, 1 / 2 / 4 pixels per lane, 20,000 Gaussians of 2 to 18 tiles each and 8,192 of
+// 8 to 240):
+//   64 tiles   270 / 408 / 772 and 95 / 120 / 184,
+//   475 tiles   95 / 138 / 220 and 56 / 71 / 101,
+//   1200 tiles  80 / 106 / 166 and 75 / 68 / 90,
+//   1536 tiles  78 / 99 / 151 and 83 / 80 / 88,
+//   1900 tiles  78 / 99 / 149 and 93 / 82 / 88,
+//   3072 tiles  92 / 93 / 134 and 128 / 106 / 96
+// and the forward kernel: 64 tiles 43 / 75, 600 tiles 62 / 89, 1200 tiles 62 / 76,
+//   1900 tiles 87 / 90, 2560 tiles 91 / 92, 3200 tiles 121 / 115
 inline int fwd_pix(int n_tiles) { return n_tiles <= 2048 ? 1 : 2; }
 inline int bwd_pix(int n_tiles) { return n_tiles <= 1536 ? 1 : n_tiles <= 3072 ? 2 : 4; }
 
@@ -183,13 +188,11 @@ __device__ __forceinline__ void mean_terms(const StagedBwd& s, float dx, float p
 // merged per lane swap, and the other moments in dx are products of the column
 // sums. Within the rows, DPP sums take two registers (8 lanes each) and a third
 // (every other quad) at once. The sum of entry e ends in lane
-// reduce_src_lane(e); one LDS permute brings the nine into the first lanes, so
-// that their atomics stay one request per 64 bytes (from four rows they are
-// four, which at 3M Gaussians costs 0.09 ms). About 25 vector instructions, where a
-// butterfly of selects and permutes over nine values took 46. Every lane of the
-// wave must call it (a disabled DPP source lane reads 0).
+// reduce_src_lane(e). About 25 vector instructions, where a butterfly of selects
+// and permutes over nine values took 46. Every lane of the wave must call it (a
+// disabled DPP source lane reads 0).
 __device__ __forceinline__ float wave_reduce9(float p0, float p1, float p2, float gx, float gy, float c0, float c1,
-                                              float c2, float dx, bool upper, bool hi8, bool odd4, int src_byte)
+                                              float c2, float dx, bool upper, bool hi8, bool odd4)
 {
     const float s1 = merge16(merge32(p0, p1), merge32(c0, c1));   // rows: p0, c0, p1, c1
     const float s2 = merge16(merge32(gx, gy), merge32(p2, c2));   // rows: gx, p2, gy, c2
@@ -203,8 +206,7 @@ __device__ __forceinline__ float wave_reduce9(float p0, float p1, float p2, floa
     const float m = h + dpp_f32<0x141>(h), m3 = h3 + dpp_f32<0x141>(h3);      // row_half_mirror
     const float q = odd4 ? m3 : m;
     const float t = q + dpp_f32<0xB1>(q);                                     // quad_perm, lane ^ 1
-    const float u = t + dpp_f32<0x4E>(t);                                     // lane ^ 2
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(src_byte, __float_as_int(u)));
+    return t + dpp_f32<0x4E>(t);                                              // lane ^ 2
 }
 
 // row[lane] += v with a wave-uniform row: its address is kept in scalar
@@ -217,13 +219,23 @@ __device__ __forceinline__ void add_scalar_row(float* row, int lane, float v)
     __hip_atomic_fetch_add(p + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+constexpr int kReduceLane[kAccStride] = {0, 8, 40, 4, 36, 24, 16, 48, 56};
+
 // The lane whose sum is entry e: M0, mean x, mean y, Mxx, Mxy, Myy, c0, c1, c2.
 __device__ __forceinline__ int reduce_src_lane(int e)
 {
-    constexpr int src[kAccStride] = {0, 8, 40, 4, 36, 24, 16, 48, 56};
     int r = 0;
 #pragma unroll
-    for (int k = 0; k < kAccStride; ++k) r = e == k ? src[k] : r;
+    for (int k = 0; k < kAccStride; ++k) r = e == k ? kReduceLane[k] : r;
+    return r;
+}
+
+// The entry whose sum is in this lane, or -1.
+__device__ __forceinline__ int reduce_entry(int lane)
+{
+    int r = -1;
+#pragma unroll
+    for (int k = 0; k < kAccStride; ++k) r = lane == kReduceLane[k] ? k : r;
     return r;
 }
 
@@ -437,8 +449,9 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
 // A_{i+1}), the background at the back):  dL/dcolour_i = alpha_i T_i g,
 // dL/dalpha_i = T_i (c_i . g - A_{i+1}). The alpha and skip decisions reuse the
 // forward's code, so the same splats are found contributing. Each lane sums its
-// pixels' terms, the wave its lanes (wave_reduce9), and nine lanes issue one
-// set of float atomics per (wave, splat).
+// pixels' terms, the wave its lanes (wave_reduce9), and a tile issues one set of
+// nine float atomics per splat: its one wave by itself, several after their sums
+// met in LDS.
 //
 // Bound by vector instruction issue: on the 3M-Gaussian 1600x1064 scene it takes
 // 0.283 ms, of which its instructions alone (156M wave instructions at 4 cycles;
@@ -448,6 +461,53 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
 // the recursion in A (no division beside T's), the alpha test on logarithms,
 // constants taken by the staging lane, lane masks combined as scalars, scalar
 // atomic addresses, and fewer instructions in the reduction.
+
+// The sums of a tile's waves over a span of kRows list entries, one entry per
+// thread of the workgroup, so that a tile issues one set of atomics per splat
+// whatever its number of waves. Splats that many tiles share (a scene's first,
+// large ones, or a few among small ones) bind the kernel by these atomics, which
+// go to the same few lines of memory: one set per wave took 124 us where 8,192
+// Gaussians are in the lists of 840 of 1,200 tiles each, one per tile 52 (4 pixels
+// per lane, one wave per tile: 49). The waves meet once per span, which costs most
+// where few tiles have long lists of small splats (20,000 Gaussians of 2 tiles each
+// in 16 tiles: 401 -> 506 us, in 475 tiles 93 -> 95).
+template <int kRows>
+struct TileSums {
+    float v[kRows * kAccStride];
+    uint32_t id[kRows];
+    uint32_t stop[4];
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int i = 0; i < kAccStride; ++i) v[i * kRows + threadIdx.x] = 0.f;
+    }
+    __device__ __forceinline__ void add(int row, int entry, float x)
+    {
+        __hip_atomic_fetch_add(&v[row * kAccStride + entry], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // By the whole workgroup: the sums that are not zero into the accumulators of
+    // their Gaussians (my_id: the span's entry threadIdx.x), then cleared. Consecutive
+    // lanes take consecutive entries of a row.
+    __device__ __forceinline__ void flush(uint32_t my_id, float* __restrict__ acc)
+    {
+        id[threadIdx.x] = my_id;
+        __syncthreads();
+#pragma unroll 3   // all nine at once take 24 registers more
+        for (int i = 0; i < kAccStride; ++i) {
+            const int k = i * kRows + (int)threadIdx.x, row = k / kAccStride;
+            const float x = v[k];
+            v[k] = 0.f;
+            if (x != 0.f)
+                __hip_atomic_fetch_add(acc + (size_t)id[row] * kAccStride + (k - row * kAccStride), x, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+    }
+};
+
+template <>
+struct TileSums<0> {};
 
 template <int kPix>
 __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, const gs_splat* __restrict__ splats,
@@ -505,15 +565,43 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
     // list positions [0, stop) can contribute
     for (int o = 32; o > 0; o >>= 1) stop = max(stop, (uint32_t)__shfl_xor((int)stop, o));
     stop = (uint32_t)__builtin_amdgcn_readfirstlane((int)stop);   // uniform: the walk's control stays scalar
-    if (stop == 0) return;
     const int nbatch = (int)((stop + kWave - 1) / kWave);
+    // several waves per tile: their sums meet in LDS (TileSums) and the tile issues
+    // one set of atomics per splat, for spans of kBatches batches
+    constexpr int kWaves = kTile * kTile / kPix / kWave, kBatches = kWaves;
+    __shared__ TileSums<(kWaves > 1 ? kBatches * kWave : 0)> sums;
+    int spans = 1;
+    if constexpr (kWaves > 1) {
+        if (lane == 0) sums.stop[wave] = stop;
+        sums.clear();
+        __syncthreads();
+        uint32_t tile_stop = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) tile_stop = max(tile_stop, sums.stop[w]);
+        spans = __builtin_amdgcn_readfirstlane((int)((tile_stop + kBatches * kWave - 1) / (kBatches * kWave)));
+    } else if (stop == 0) {
+        return;
+    }
     // each batch of 64 list entries is staged in LDS and read back one record
     // per step at a uniform address (broadcast), as in the forward
     __shared__ StageSlot stage[kTile * kTile / kPix / kWave];
     StageSlot& st = stage[wave];
-    // lane roles of the reduction (wave_reduce9); lanes 0..8 add one entry each
+    // lane roles of the reduction (wave_reduce9)
     const bool red_up = lane & 32, red_hi8 = lane & 8, red_odd4 = lane & 4;
-    const int red_src = 4 * reduce_src_lane(lane);
+    // A splat's nine sums into its row: of the tile's sums in LDS, from the lanes
+    // that hold them; or of the accumulators, gathered into lanes 0..8 by one LDS
+    // permute, so that the atomics stay one request per 64 bytes (from four rows of
+    // lanes they are four, which at 3M Gaussians costs 0.09 ms).
+    const int red_lane = kWaves > 1 ? reduce_entry(lane) : 4 * reduce_src_lane(lane);
+    auto add_sums = [&](float u, int span_row, uint32_t batch_id, int j) {
+        if constexpr (kWaves > 1) {
+            if (red_lane >= 0) sums.add(span_row + j, red_lane, u);
+        } else {
+            const float t = __int_as_float(__builtin_amdgcn_ds_bpermute(red_lane, __float_as_int(u)));
+            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, j);
+            if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t);
+        }
+    };
     float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0, c2 = c0;
     uint32_t cid = 0, nid = 0;   // nid: the list entry of the batch after the prefetched one, loaded a batch early
     {
@@ -525,141 +613,150 @@ __global__ __launch_bounds__(kTile * kTile / kPix) void k_blend_bwd(Cam cam, con
         }
         if (nbatch >= 2) nid = values[start + (uint32_t)(nbatch - 2) * kWave + lane];
     }
-    for (int bi = nbatch - 1; bi >= 0; --bi) {
-        const uint32_t b = (uint32_t)bi * kWave;
-        stage_words_bwd(c0, c1, c2, st.w[0][lane], st.w[1][lane], st.w[2][lane]);
-        const uint32_t batch_id = cid;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int cnt = (int)min((uint32_t)kWave, stop - b);
-        // a splat that reaches alpha >= 1/255 nowhere in this wave's pixels
-        // passes nothing back: each lane tests the record it holds (the
-        // conservative bounding box, then the ellipse), and the walk visits only
-        // the others, back to front
-        uint64_t todo = __ballot(lane < cnt && fabsf(c0.x - box_cx) <= c2.z + box_hx &&
-                                 fabsf(c0.y - box_cy) <= c2.w + box_hy &&
-                                 ellipse_meets_box(c0.x, c0.y, c0.z, c0.w, c1.x, c2.y, box_cx - box_hx,
-                                                   box_cx + box_hx, box_lo, box_hi));
-        if (bi > 0) {
-            cid = nid;
-            const float4* r = reinterpret_cast<const float4*>(splats + cid);
-            c0 = r[0]; c1 = r[1]; c2 = r[2];
-            if (bi > 1) nid = values[start + b - 2 * kWave + lane];
+    int bi = nbatch - 1;
+    for (int span = spans - 1; span >= 0; --span) {
+        // the span's list entries, needed when it is flushed
+        [[maybe_unused]] uint32_t span_id = 0;
+        if constexpr (kWaves > 1) {
+            const uint32_t p = (uint32_t)span * (kBatches * kWave) + threadIdx.x;
+            if (p < len) span_id = values[start + p];
         }
-        if constexpr (kPix == 1) {
-            // few tiles: kBwdGroup splats a step, without branches, as in the forward;
-            // the transmittance and the colour behind go from one to the next. A
-            // lane that a splat does not reach takes its values by selects (a
-            // product with zero would pass on an infinite colour or gradient).
-            while (todo != 0) {
-                StagedBwd s[kBwdGroup];
-                float dx[kBwdGroup], dy[kBwdGroup], oG[kBwdGroup], alpha[kBwdGroup], inv[kBwdGroup];
-                uint64_t in[kBwdGroup];
-                int js[kBwdGroup];
-                int j = 0;
+        for (; bi >= span * kBatches; --bi) {
+            const uint32_t b = (uint32_t)bi * kWave;
+            const int span_row = (bi - span * kBatches) * kWave;
+            stage_words_bwd(c0, c1, c2, st.w[0][lane], st.w[1][lane], st.w[2][lane]);
+            const uint32_t batch_id = cid;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int cnt = (int)min((uint32_t)kWave, stop - b);
+            // a splat that reaches alpha >= 1/255 nowhere in this wave's pixels
+            // passes nothing back: each lane tests the record it holds (the
+            // conservative bounding box, then the ellipse), and the walk visits only
+            // the others, back to front
+            uint64_t todo = __ballot(lane < cnt && fabsf(c0.x - box_cx) <= c2.z + box_hx &&
+                                     fabsf(c0.y - box_cy) <= c2.w + box_hy &&
+                                     ellipse_meets_box(c0.x, c0.y, c0.z, c0.w, c1.x, c2.y, box_cx - box_hx,
+                                                       box_cx + box_hx, box_lo, box_hi));
+            if (bi > 0) {
+                cid = nid;
+                const float4* r = reinterpret_cast<const float4*>(splats + cid);
+                c0 = r[0]; c1 = r[1]; c2 = r[2];
+                if (bi > 1) nid = values[start + b - 2 * kWave + lane];
+            }
+            if constexpr (kPix == 1) {
+                // few tiles: kBwdGroup splats a step, without branches, as in the forward;
+                // the transmittance and the colour behind go from one to the next. A
+                // lane that a splat does not reach takes its values by selects (a
+                // product with zero would pass on an infinite colour or gradient).
+                while (todo != 0) {
+                    StagedBwd s[kBwdGroup];
+                    float dx[kBwdGroup], dy[kBwdGroup], oG[kBwdGroup], alpha[kBwdGroup], inv[kBwdGroup];
+                    uint64_t in[kBwdGroup];
+                    int js[kBwdGroup];
+                    int j = 0;
 #pragma unroll
-                for (int g = 0; g < kBwdGroup; ++g) {
-                    const uint64_t some = todo != 0 ? ~0ull : 0ull;   // none left: the last one again, masked out
-                    j = todo != 0 ? 63 - (int)__builtin_clzll(todo) : j;
-                    todo &= ~(1ull << j);
-                    s[g] = staged_bwd(st.w[0][j], st.w[1][j], st.w[2][j]);
-                    js[g] = j;
-                    in[g] = some;
+                    for (int g = 0; g < kBwdGroup; ++g) {
+                        const uint64_t some = todo != 0 ? ~0ull : 0ull;   // none left: the last one again, masked out
+                        j = todo != 0 ? 63 - (int)__builtin_clzll(todo) : j;
+                        todo &= ~(1ull << j);
+                        s[g] = staged_bwd(st.w[0][j], st.w[1][j], st.w[2][j]);
+                        js[g] = j;
+                        in[g] = some;
+                    }
+#pragma unroll
+                    for (int g = 0; g < kBwdGroup; ++g) {
+                        dx[g] = px - s[g].mx;
+                        dy[g] = py[0] - s[g].my;
+                        const float e = quad_neg_power(s[g], column_quad(s[g], dx[g]), dy[g]);
+                        in[g] &= __ballot(b + (uint32_t)js[g] < last[0]) & __ballot(in_reach(e, s[g].e_max));
+                        oG[g] = s[g].op * __builtin_amdgcn_exp2f(-e);
+                        alpha[g] = __builtin_amdgcn_inverse_ballot_w64(in[g]) ? fminf(kAlphaMax, oG[g]) : 0.f;
+                        inv[g] = __builtin_amdgcn_rcpf(1.f - alpha[g]);
+                    }
+                    float p0[kBwdGroup], p1[kBwdGroup], p2[kBwdGroup], ac0[kBwdGroup], ac1[kBwdGroup], ac2[kBwdGroup];
+#pragma unroll
+                    for (int g = 0; g < kBwdGroup; ++g) {
+                        const bool on = __builtin_amdgcn_inverse_ballot_w64(in[g]);
+                        T[0] *= inv[g];
+                        const float w = alpha[g] * T[0];
+                        ac0[g] = on ? w * g0[0] : 0.f;
+                        ac1[g] = on ? w * g1[0] : 0.f;
+                        ac2[g] = on ? w * g2[0] : 0.f;
+                        const float u =
+                            __fmaf_rn(s[g].b, g2[0], __fmaf_rn(s[g].g, g1[0], __fmaf_rn(s[g].r, g0[0], -A[0])));
+                        A[0] = on ? __fmaf_rn(alpha[g], u, A[0]) : A[0];
+                        p0[g] = on && oG[g] < kAlphaMax ? w * u : 0.f;
+                        p1[g] = p0[g] * dy[g];
+                        p2[g] = p1[g] * dy[g];
+                    }
+                    float t[kBwdGroup];
+#pragma unroll
+                    for (int g = 0; g < kBwdGroup; ++g) {
+                        float gx, gy;
+                        mean_terms(s[g], dx[g], p0[g], p1[g], gx, gy);
+                        t[g] = wave_reduce9(p0[g], p1[g], p2[g], gx, gy, ac0[g], ac1[g], ac2[g], dx[g], red_up, red_hi8,
+                                            red_odd4);
+                    }
+#pragma unroll
+                    for (int g = 0; g < kBwdGroup; ++g) {
+                        if (in[g] == 0) continue;
+                        add_sums(t[g], span_row, batch_id, js[g]);
+                    }
                 }
+            } else {
+                while (todo != 0) {
+                    const int j = 63 - (int)__builtin_clzll(todo);
+                    todo ^= 1ull << j;
+                    const uint32_t pos = b + (uint32_t)j;
+                    const StagedBwd s = staged_bwd(st.w[0][j], st.w[1][j], st.w[2][j]);
+                    const float dx = px - s.mx;
+                    const Quad q = column_quad(s, dx);
+                    // per-lane sums over its pixels: colour gradient and dL/dpower times
+                    // 1, dy, dy^2 (the lane's pixels share dx)
+                    float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f;
+                    float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+                    uint64_t any = 0;
 #pragma unroll
-                for (int g = 0; g < kBwdGroup; ++g) {
-                    dx[g] = px - s[g].mx;
-                    dy[g] = py[0] - s[g].my;
-                    const float e = quad_neg_power(s[g], column_quad(s[g], dx[g]), dy[g]);
-                    in[g] &= __ballot(b + (uint32_t)js[g] < last[0]) & __ballot(in_reach(e, s[g].e_max));
-                    oG[g] = s[g].op * __builtin_amdgcn_exp2f(-e);
-                    alpha[g] = __builtin_amdgcn_inverse_ballot_w64(in[g]) ? fminf(kAlphaMax, oG[g]) : 0.f;
-                    inv[g] = __builtin_amdgcn_rcpf(1.f - alpha[g]);
-                }
-                float p0[kBwdGroup], p1[kBwdGroup], p2[kBwdGroup], ac0[kBwdGroup], ac1[kBwdGroup], ac2[kBwdGroup];
-#pragma unroll
-                for (int g = 0; g < kBwdGroup; ++g) {
-                    const bool on = __builtin_amdgcn_inverse_ballot_w64(in[g]);
-                    T[0] *= inv[g];
-                    const float w = alpha[g] * T[0];
-                    ac0[g] = on ? w * g0[0] : 0.f;
-                    ac1[g] = on ? w * g1[0] : 0.f;
-                    ac2[g] = on ? w * g2[0] : 0.f;
-                    const float u = __fmaf_rn(s[g].b, g2[0], __fmaf_rn(s[g].g, g1[0], __fmaf_rn(s[g].r, g0[0], -A[0])));
-                    A[0] = on ? __fmaf_rn(alpha[g], u, A[0]) : A[0];
-                    p0[g] = on && oG[g] < kAlphaMax ? w * u : 0.f;
-                    p1[g] = p0[g] * dy[g];
-                    p2[g] = p1[g] * dy[g];
-                }
-                float t[kBwdGroup];
-#pragma unroll
-                for (int g = 0; g < kBwdGroup; ++g) {
+                    for (int k = 0; k < kPix; ++k) {
+                        // one branch per pixel (no short circuit); the cap is a select inside it
+                        const float dy = py[k] - s.my;
+                        const float e = quad_neg_power(s, q, dy);
+                        // the comparisons' lane masks, combined as scalars
+                        const uint64_t reach = __ballot(pos < last[k]) & __ballot(in_reach(e, s.e_max));
+                        any |= reach;
+                        if (!__builtin_amdgcn_inverse_ballot_w64(reach)) continue;
+                        const float oG = s.op * __builtin_amdgcn_exp2f(-e);
+                        const float alpha = fminf(kAlphaMax, oG);
+                        // hardware reciprocal (1 ulp): T is recovered over a few hundred
+                        // splats, so its relative error stays near 1e-5
+                        T[k] *= __builtin_amdgcn_rcpf(1.f - alpha);   // transmittance in front of this splat
+                        const float w = alpha * T[k];
+                        a_c0 = __fmaf_rn(w, g0[k], a_c0);
+                        a_c1 = __fmaf_rn(w, g1[k], a_c1);
+                        a_c2 = __fmaf_rn(w, g2[k], a_c2);
+                        // colour less what it hides, on g: dL/dalpha = T u
+                        const float u = __fmaf_rn(s.b, g2[k], __fmaf_rn(s.g, g1[k], __fmaf_rn(s.r, g0[k], -A[k])));
+                        A[k] = __fmaf_rn(alpha, u, A[k]);
+                        // dL/dpower = alpha dL/dalpha below the cap; a capped entry passes nothing
+                        const float dpow = oG < kAlphaMax ? w * u : 0.f;
+                        const float pdy = dpow * dy;
+                        p0 += dpow;
+                        p1 += pdy;
+                        p2 = __fmaf_rn(pdy, dy, p2);
+                    }
+                    if (any == 0) continue;
                     float gx, gy;
-                    mean_terms(s[g], dx[g], p0[g], p1[g], gx, gy);
-                    t[g] = wave_reduce9(p0[g], p1[g], p2[g], gx, gy, ac0[g], ac1[g], ac2[g], dx[g], red_up, red_hi8,
-                                        red_odd4, red_src);
-                }
-#pragma unroll
-                for (int g = 0; g < kBwdGroup; ++g) {
-                    if (in[g] == 0) continue;
-                    const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, js[g]);
-                    if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t[g]);
+                    mean_terms(s, dx, p0, p1, gx, gy);
+                    add_sums(wave_reduce9(p0, p1, p2, gx, gy, a_c0, a_c1, a_c2, dx, red_up, red_hi8, red_odd4),
+                             span_row, batch_id, j);
                 }
             }
-        } else {
-            while (todo != 0) {
-                const int j = 63 - (int)__builtin_clzll(todo);
-                todo ^= 1ull << j;
-                const uint32_t pos = b + (uint32_t)j;
-                const StagedBwd s = staged_bwd(st.w[0][j], st.w[1][j], st.w[2][j]);
-                const float dx = px - s.mx;
-                const Quad q = column_quad(s, dx);
-                // per-lane sums over its pixels: colour gradient and dL/dpower times
-                // 1, dy, dy^2 (the lane's pixels share dx)
-                float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f;
-                float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-                uint64_t any = 0;
-#pragma unroll
-                for (int k = 0; k < kPix; ++k) {
-                    // one branch per pixel (no short circuit); the cap is a select inside it
-                    const float dy = py[k] - s.my;
-                    const float e = quad_neg_power(s, q, dy);
-                    // the comparisons' lane masks, combined as scalars
-                    const uint64_t reach = __ballot(pos < last[k]) & __ballot(in_reach(e, s.e_max));
-                    any |= reach;
-                    if (!__builtin_amdgcn_inverse_ballot_w64(reach)) continue;
-                    const float oG = s.op * __builtin_amdgcn_exp2f(-e);
-                    const float alpha = fminf(kAlphaMax, oG);
-                    // hardware reciprocal (1 ulp): T is recovered over a few hundred
-                    // splats, so its relative error stays near 1e-5
-                    T[k] *= __builtin_amdgcn_rcpf(1.f - alpha);   // transmittance in front of this splat
-                    const float w = alpha * T[k];
-                    a_c0 = __fmaf_rn(w, g0[k], a_c0);
-                    a_c1 = __fmaf_rn(w, g1[k], a_c1);
-                    a_c2 = __fmaf_rn(w, g2[k], a_c2);
-                    // colour less what it hides, on g: dL/dalpha = T u
-                    const float u = __fmaf_rn(s.b, g2[k], __fmaf_rn(s.g, g1[k], __fmaf_rn(s.r, g0[k], -A[k])));
-                    A[k] = __fmaf_rn(alpha, u, A[k]);
-                    // dL/dpower = alpha dL/dalpha below the cap; a capped entry passes nothing
-                    const float dpow = oG < kAlphaMax ? w * u : 0.f;
-                    const float pdy = dpow * dy;
-                    p0 += dpow;
-                    p1 += pdy;
-                    p2 = __fmaf_rn(pdy, dy, p2);
-                }
-                if (any == 0) continue;
-                float gx, gy;
-                mean_terms(s, dx, p0, p1, gx, gy);
-                const float t = wave_reduce9(p0, p1, p2, gx, gy, a_c0, a_c1, a_c2, dx, red_up, red_hi8, red_odd4,
-                                             red_src);
-                const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)batch_id, j);
-                if (lane < kAccStride) add_scalar_row(acc + (size_t)id * kAccStride, lane, t);
-            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if constexpr (kWaves > 1) sums.flush(span_id, acc);
     }
 }
 

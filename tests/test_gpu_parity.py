@@ -244,6 +244,26 @@ def test_mean_gradient_of_long_thin_splats(long_px, short_px, size):
     assert error(gpu) <= 1.5 * error(fp32) + 1e-6
 
 
+@pytest.mark.parametrize("n,tiles", [(1, (1, 1)), (127, (1, 1)), (255, (2, 1)), (256, (1, 2)), (257, (1, 1)),
+                                     (1025, (2, 2)), (128, (32, 49)), (129, (39, 40)), (300, (40, 39))])
+def test_backward_spans(n, tiles):
+    # the waves of a tile add up their sums over 256 list entries (128 above 1,536
+    # tiles): lists that end at, before and behind such a span's end, walked to
+    # their end by every wave, or by some (a part of the splats is opaque or small)
+    w, h = 16 * tiles[0] - 3, 16 * tiles[1] - 5
+    cam = tiny_camera(w, h, bg=(0.2, 0.4, 0.1))
+    sc = inputs.make_scene("tiny", n=n)
+    sc.means[:] *= np.float32(0.2)
+    sc.log_scales[:] = np.float32(np.log(6.0 * max(w, h) / cam.fx))
+    sc.opacity_logits[:] = -4.8
+    sc.log_scales[:, ::5] = np.float32(np.log(6.0 / cam.fx))
+    sc.log_scales[:] -= np.float32([[0.0], [0.3], [0.6]])   # equal scales would have no rotation gradient
+    sc.opacity_logits[7::50] = 1.0
+    # flat splats cross a threshold slowly: the pixels within the rounding bound are
+    # a strip of up to 0.1 pixels along n / 5 contours of up to 2 (w + h)
+    check_all(sc, cam, label="spans-%d-%dx%d" % (n, *tiles), max_flagged=max(n // 5 * 2 * (w + h) // 10, w * h // 250))
+
+
 @pytest.mark.parametrize("degree", [3, 1])
 def test_sh3_backward_without_the_colour_jacobian(degree):
     # gs_preprocessed.color_jac NULL: the preprocess writes no view-direction
