@@ -114,6 +114,36 @@ def test_depth_sort_workgroups(n, size):
     compare_lists(gpu, values, tiles, ranges)
 
 
+@pytest.mark.parametrize("n,size", [(8192 * 1024, (320, 240)), (8192 * 1024 + 1, (320, 240)),
+                                    (8192 * 1024 + 1, (64, 4112))])
+def test_entry_offsets_of_many_chunks(n, size):
+    # up to 8,192 chunks of 1,024 Gaussians every workgroup adds up the totals of the
+    # chunks before its own, above that a launch scans them: both sides of the line,
+    # with rectangles packed in 32 bits and (257 tiles a side) gathered; 128 copies of
+    # the same Gaussians, so that every depth ties, three in four of them culled;
+    # device and host mode, a capacity too small
+    sc = inputs.make_scene("tiny", n=65537, appearance=("nasg",)).subset(np.arange(n) % 65537)
+    sc.means[2, np.arange(n) % 4 != 1] = -4.0
+    cam = tiny_camera(*size)
+    sc.log_scales[:] = np.float32(np.log(0.1 / cam.fx))
+    gpu = run_gpu(sc, cam, "nasg", 0, capacity=1 << 25)
+    values, tiles, ranges = orc.bin_sort(cam, orc.preprocess(cam, sc, kind="nasg", sh_degree=0))
+    compare_lists(gpu, values, tiles, ranges)
+    cs, st, P = gs.camera_struct(cam), gpu["scene_tensors"], gpu["P"]
+    for capacity in (P, P - 1):
+        fr = gs.Frame(n, cam.width, cam.height, gs.GS_APP_NASG, capacity)
+        gs.gs_preprocess(cs, st.gaussians(), st.appearance(gs.GS_APP_NASG, 0), fr.pre, fr.workspace, fr.ws_bytes,
+                         sync_pairs=False)
+        gs.gs_bin_sort(cs, fr.pre, n, gs.GS_PAIRS_ON_DEVICE, capacity, fr.values, None, fr.ranges, fr.workspace,
+                       fr.ws_bytes)
+        got = fr.ranges.cpu().numpy().reshape(-1, 2).astype(np.int64)
+        if capacity == P:
+            assert np.array_equal(got, ranges)
+            assert np.array_equal(fr.values.cpu().numpy()[:P].astype(np.int64), values.astype(np.int64))
+        else:
+            assert not got.any() and int(fr.num_pairs.item()) == P
+
+
 @pytest.mark.parametrize("n,size", [(1, (64, 64)), (1023, (64, 64)), (1025, (200, 90)), (2049, (200, 90)),
                                     (4097, (1000, 30)), (8193, (330, 200)),
                                     (12288, (330, 200)), (12289, (330, 200)), (24576, (640, 300)), (24577, (640, 300)),
