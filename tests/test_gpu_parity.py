@@ -18,9 +18,9 @@ import torch
 
 from oracle import oracle as orc
 from paper_2609_05255_amd import gsraster as gs
-from parity import (MLP_ATOL, MLP_HALF_ATOL, MLP_GRADS, NEURAL_FLIP, check_grads, compare_image, compare_lists,
-                    compare_preprocess, flagged_pixels, grad_stats, lobe_color_atol, report_grads, run_gpu, say,
-                    tiny_camera)
+from parity import (GRAD_ELEM_FLOOR, GRAD_ELEM_RTOL, MLP_ATOL, MLP_HALF_ATOL, MLP_GRADS, NEURAL_FLIP, check_grads,
+                    compare_image, compare_lists, compare_preprocess, flagged_pixels, grad_stats, lobe_color_atol,
+                    report_grads, run_gpu, say, tiny_camera)
 
 pytestmark = pytest.mark.gpu
 
@@ -292,6 +292,36 @@ def test_backward_spans(n, tiles):
     # flat splats cross a threshold slowly: the pixels within the rounding bound are
     # a strip of up to 0.1 pixels along n / 5 contours of up to 2 (w + h)
     check_all(sc, cam, label="spans-%d-%dx%d" % (n, *tiles), max_flagged=max(n // 5 * 2 * (w + h) // 10, w * h // 250))
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("tiles", [(4, 4), (40, 40), (64, 49)])
+def test_backward_keeps_a_pixel_to_its_splats(tiles, value):
+    # an infinite or undefined upstream gradient at one pixel (1, 2 and 4 pixels per
+    # lane): the Gaussians that are blended there take it, and no other Gaussian's
+    # gradient changes, also of those that share its lane, wave and list
+    cam = tiny_camera(16 * tiles[0], 16 * tiles[1])
+    sc = inputs.make_scene("tiny")
+    pre = orc.preprocess(cam, sc)
+    values, _, ranges = orc.bin_sort(cam, pre)
+    n_contrib, margin = orc.render_fwd(cam, pre, ranges, values)[2:]
+    y, x = np.unravel_index(np.argmax(np.where(margin > 1.0, n_contrib, -1)), margin.shape)
+    g = inputs.make_upstream_grad(cam.width, cam.height)
+    g[:, y, x] = 0.0
+    one = np.zeros_like(g)
+    one[:, y, x] = 1.0
+    there = orc.render_bwd(cam, sc, pre, ranges, values, one)["dcolor"].any(axis=0)
+    listed = ranges[y // 16 * tiles[0] + x // 16] @ (-1, 1)
+    clean = run_gpu(sc, cam, "sh3", 3, g, capacity=values.size)["grads"]
+    g[:, y, x] = value
+    got = run_gpu(sc, cam, "sh3", 3, g, capacity=values.size)["grads"]
+    say("case one pixel %s of %dx%d tiles: %d Gaussians blended there, %d in its tile's list, of %d" % (
+        value, *tiles, there.sum(), listed, sc.n))
+    assert 0 < there.sum() < listed and not np.isfinite(got["dsh"][:3, there]).any()
+    for k, ref in clean.items():
+        # the atomics' order: as the parity bar
+        bound = GRAD_ELEM_RTOL * np.abs(ref) + GRAD_ELEM_FLOOR * np.abs(ref).max()
+        assert (np.abs(got[k] - ref) <= bound)[..., ~there].all(), k
 
 
 @pytest.mark.parametrize("degree", [3, 1])
