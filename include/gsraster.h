@@ -449,7 +449,10 @@ enum {
     GS_KERNEL_BLOCK_ENTRIES, GS_KERNEL_BLOCK_SORT, GS_KERNEL_TILE_LISTS, GS_KERNEL_BLEND_FWD,
     GS_KERNEL_BWD_PREP, GS_KERNEL_BLEND_BWD, GS_KERNEL_PREPROCESS_BWD, GS_KERNEL_MLP_REDUCE,
     GS_KERNEL_ADAM, GS_KERNEL_NEURAL_FOLD, GS_KERNEL_COUNT
-};   /* GS_KERNEL_BWD_PREP: the backward's accumulator clear and its tile order */
+};   /* GS_KERNEL_BWD_PREP: the backward's accumulator clear and its tile order.
+      * gs_bin_sort of few Gaussians (its method's second form) has no block
+      * entries: GS_KERNEL_ENTRY_OFFSETS, _BLOCK_ENTRIES and _BLOCK_SORT count
+      * nothing then, and _TILE_LISTS is the search and the lists together. */
 typedef struct gs_timer gs_timer;
 gs_status gs_timer_create(gs_timer** out);
 gs_status gs_timer_destroy(gs_timer* timer);

@@ -328,7 +328,8 @@ __device__ __forceinline__ void store4(T* p, V v, int rem)
 // steps them); a gradient array of `a` that is not NULL still receives the
 // gradient.
 //
-// Bound by memory: 1,452 bytes per Gaussian in 118 read and 118 written rows.
+// Bound by memory: 1,452 bytes per Gaussian, 177 rows read and 177 written (59
+// parameters and their two moments) and the 36-byte accumulator.
 // With a Gaussian per lane throughout, a wave moved 256 bytes of a row at a time
 // and reached 4.5 TB/s (0.957 ms at 3M Gaussians). Here the workgroup's 256
 // Gaussians go through their 48 coefficient rows with four Gaussians per lane, a

@@ -76,9 +76,11 @@ __device__ __forceinline__ void stage_words(const float4& c0, const float4& c1, 
 {
     w0 = make_float4(c0.x, c0.y, (0.5f * kLog2e) * c0.z, kLog2e * c0.w);
     w1 = make_float4((0.5f * kLog2e) * c1.x, c1.y, c1.z, c1.w);
-    // the hardware logarithm corrected by the residual of its exponential: within
-    // half an ulp and a few 1e-8, so that the alpha test decides as closely on the
-    // logarithms as o e^power >= 1/255 does
+    // the hardware logarithm corrected by the residual of its exponential. Over all
+    // opacities above 1/255 it is within 3.9e-7 of log2(255 o), and within 1.9e-7
+    // below 2/255 (measured): 2.7e-7 and 1.3e-7 of alpha. The hardware exponential
+    // and the product of o e^power >= 1/255 are within 1.8e-7, so the test decides
+    // about as closely on the logarithms.
     const float r255 = 255.f * c1.y;
     const float l = __builtin_amdgcn_logf(r255);
     const float reach = __fmaf_rn(__fmaf_rn(r255, __builtin_amdgcn_exp2f(-l), -1.f), kLog2e, l);

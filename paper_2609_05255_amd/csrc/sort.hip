@@ -444,10 +444,12 @@ static hipError_t block_radix_pass(const uint32_t* keys_in, const uint32_t* vals
     return hipGetLastError();
 }
 
-// Keys per thread of the block sort: 8, or 16 where the capacity tells of
+// Keys per thread of the block sort: 8, or 16 where the capacity leaves room for
 // millions of entries (about a quarter of the pairs), for longer runs per digit
 // (scatter 12 us with 8 and 18 with 16 at 0.3M entries, 62 and 54 at 6.5M, 104
-// and 82 at 11M).
+// and 82 at 11M). The number of entries is only known on the device: a buffer
+// with room for many more pairs than there are gets 16 by its size (0.33M pairs:
+// the whole binning 96 us with the capacity they need, 104 at 16M, 109 at 64M).
 static int block_items(uint64_t capacity) { return capacity <= (12u << 20) ? kBlockSortItems : 2 * kBlockSortItems; }
 
 // ---- block entries in depth order -------------------------------------------
@@ -1284,11 +1286,15 @@ int radix_groups(int64_t keys, int tile)
     return (int)div_up(nblocks, radix_group(nblocks));
 }
 
-// Keys per thread of the depth sort's passes (1,024 threads): the fewest that
-// make at most one workgroup per compute unit, so that every unit works and a
-// digit's runs are as long as that allows; 12 for more keys than that (scatters
-// at 3M Gaussians: 145 us with 8, 118 with 12; at 6M 290 with 8, 273 with 12,
-// 319 with 16, which spill).
+// Keys per thread of the depth sort's passes (1,024 threads), of 4, 8 and 12: the
+// fewest that make at most one workgroup per compute unit (256), so that no unit
+// has a second one to itself; 12 for more keys than that, whose runs per digit are
+// the longest. The whole binning with 4 / 8 / 12, us, at 1600x1064: 1.00M Gaussians
+// 136 / 156 / 176, 1.06M 162 / 158 / 178, 2.10M (2^21) 222 / 208 / 222, 2.11M
+// 248 / 253 / 226, 3M 309 / 307 / 282, 6M 559 / 513 / 495. Scatters at 6M: 290 with
+// 8, 273 with 12, 319 with 16, which spill. (Rectangles gathered, on grids beyond
+// 256 tiles a side: the same lines; 12 with 8M and more is 3% behind workgroups of
+// 4,096 keys, 588 against 568.)
 int depth_items(int64_t n) { return n <= (1 << 20) ? 4 : n <= (1 << 21) ? 8 : 12; }
 
 // Depth sort of the n Gaussians and their tile rectangles. On grids of at most
