@@ -456,7 +456,7 @@ hipError_t launch_blend_fwd(const Cam& cam, const gs_splat* splats, const uint32
 // met in LDS.
 //
 // Bound by vector instruction issue: on the 3M-Gaussian 1600x1064 scene it takes
-// 0.283 ms, of which its instructions alone (156M wave instructions at 4 cycles;
+// 0.277 ms, of which its instructions alone (156M wave instructions at 4 cycles;
 // the two transcendentals per pixel take 16) fill 0.25 ms or more. What shortened it
 // (from 0.318 ms and 204M): second moments summed raw and their factors applied once
 // per Gaussian later, no opacity sum (dL/dopacity follows from the zeroth moment),

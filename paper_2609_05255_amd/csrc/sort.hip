@@ -3,7 +3,8 @@
 //
 // Instead of radix-sorting P 45-bit (tile, depth) keys, the Gaussians are
 // sorted once by depth (4 stable 8-bit LSD passes over n 32-bit keys with the
-// index as value, so equal depths stay in index order). Then, in that order,
+// index, and beside it the tile rectangle, as value, so equal depths stay in index
+// order). Then, in that order,
 // each Gaussian gets one entry per 4x4-tile block its rectangle meets (about a
 // quarter as many entries as pairs), a stable LSD sort on the block id groups
 // the entries by block with depth order kept inside each block, and every
