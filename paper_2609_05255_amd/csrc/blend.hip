@@ -64,17 +64,23 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // A splat as the walks read it from LDS: the record with the constants of the
 // quadratic form taken once by the lane that stages it. In base-2 units (times
-// log2 e), so that exp(power) is one hardware exp2: -power log2 e = ka dx^2 +
-// kb dx dy + kc dy^2. e_max is its bound where alpha reaches 1/255,
-// log2(255 opacity).
+// log2 e), so that exp(power) is one hardware exp2: with k = log2(e) / 2,
+// -power log2 e = k (ca dx^2 + cb2 dx dy) + kc dy^2 with cb2 = 2 b and kc = k c.
+// k goes with dx (column_quad), where its rounding differs from column to column.
+// Staged with the conic (k a, 2 k b) it is the same at every pixel of a splat and
+// adds up: for splats of sigma 60 x 0.5 pixels under a smooth upstream gradient the
+// error of the opacity's gradient was 2.5 times as large (1.1e-5 to 2.8e-5 of it, now
+// 0.5e-5 to 1.1e-5), for one vector instruction less per visit of the forward (no
+// time measured: a paper-scale render 663 us either way). e_max is the bound of
+// -power log2 e where alpha reaches 1/255, log2(255 opacity).
 struct Staged {
-    float mx, my, ka, kb, kc, op, r, g, b, e_max;
+    float mx, my, ca, cb2, kc, op, r, g, b, e_max;
 };
 
 __device__ __forceinline__ void stage_words(const float4& c0, const float4& c1, const float4& c2, float4& w0,
                                             float4& w1, float2& w2)
 {
-    w0 = make_float4(c0.x, c0.y, (0.5f * kLog2e) * c0.z, kLog2e * c0.w);
+    w0 = make_float4(c0.x, c0.y, c0.z, 2.f * c0.w);
     w1 = make_float4((0.5f * kLog2e) * c1.x, c1.y, c1.z, c1.w);
     // the hardware logarithm corrected by the residual of its exponential. Over all
     // opacities above 1/255 it is within 3.9e-7 of log2(255 o), and within 1.9e-7
@@ -92,11 +98,10 @@ __device__ __forceinline__ Staged staged(const float4& w0, const float4& w1, con
     return Staged{w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y};
 }
 
-// The backward needs the record's conic (a, b, c) as well, for the gradient of
-// the mean: a in the place of ka (one product per visit gives ka, the same bits
-// as the forward's), b and c in the third plane's spare words.
+// The backward needs the record's b and c as well, for the gradient of the mean:
+// in the third plane's spare words.
 struct StagedBwd : Staged {
-    float ca, cb, cc;
+    float cb, cc;
 };
 
 __device__ __forceinline__ void stage_words_bwd(const float4& c0, const float4& c1, const float4& c2, float4& w0,
@@ -104,15 +109,12 @@ __device__ __forceinline__ void stage_words_bwd(const float4& c0, const float4& 
 {
     float2 tail;
     stage_words(c0, c1, c2, w0, w1, tail);
-    w0.z = c0.z;
     w2 = make_float4(tail.x, tail.y, c0.w, c1.x);
 }
 
 __device__ __forceinline__ StagedBwd staged_bwd(const float4& w0, const float4& w1, const float4& w2)
 {
-    StagedBwd s{staged(w0, w1, make_float2(w2.x, w2.y)), w0.z, w2.z, w2.w};
-    s.ka = (0.5f * kLog2e) * w0.z;
-    return s;
+    return StagedBwd{staged(w0, w1, make_float2(w2.x, w2.y)), w2.z, w2.w};
 }
 
 // A wave's staged batch: three planes at one 16-byte stride, so that a splat's
@@ -127,7 +129,11 @@ struct Quad {
     float q0, q1;
 };
 
-__device__ __forceinline__ Quad column_quad(const Staged& s, float dx) { return Quad{s.ka * dx * dx, s.kb * dx}; }
+__device__ __forceinline__ Quad column_quad(const Staged& s, float dx)
+{
+    const float kdx = (0.5f * kLog2e) * dx;
+    return Quad{s.ca * dx * kdx, s.cb2 * kdx};
+}
 
 __device__ __forceinline__ float quad_neg_power(const Staged& s, const Quad& q, float dy)
 {
@@ -174,8 +180,8 @@ __device__ __forceinline__ float merge16(float a, float b)
 // error was 3 to 10 times larger (5e-6 to 9e-6 of it against 0.8e-6 to 2e-6 for
 // splats of sigma 40 x 4 pixels under a smooth upstream gradient, 4e-3 to 7e-3
 // against 1e-3 to 2e-3 at 300 x 0.1), and it took a conic other than the blended
-// record's. 6 vector instructions per visit with the staging above, 4% of the
-// backward's time at 3M Gaussians.
+// record's. 5 vector instructions per visit; with column_quad's fourth product
+// they are 4% of the backward's time at 3M Gaussians.
 __device__ __forceinline__ void mean_terms(const StagedBwd& s, float dx, float p0, float p1, float& gx, float& gy)
 {
     const float m_x = dx * p0;

@@ -274,6 +274,29 @@ def test_mean_gradient_of_long_thin_splats(long_px, short_px, size):
     assert error(gpu) <= 1.5 * error(fp32) + 1e-6
 
 
+@pytest.mark.parametrize("size", [(480, 320), (800, 608), (1600, 1064)])
+def test_opacity_gradient_of_long_thin_splats(size):
+    # the quadratic form of a long thin splat is a difference of terms up to kappa =
+    # ac / (ac - b^2) larger. A constant of the form that is rounded once per splat
+    # errs alike at every pixel: c's, by a relative d, moves the sum that is the
+    # opacity's gradient by d kappa / 2 (the mean of c dy^2 / 2 over the splat), and
+    # |d| of one product is 2.1e-8 in the median (a quarter of 2^-23, over mantissas
+    # from 1 to 2). Roundings that differ from pixel to pixel average out: 1.5 times
+    # the one constant's share. (With a's, b's and c's rounded 2.6e-8 to 3.0e-8.)
+    cam = tiny_camera(*size)
+    sc = thin_scene(160, cam, 60, 0.5)
+    pre = orc.preprocess(cam, sc)
+    values, _, ranges = orc.bin_sort(cam, pre)
+    margin = orc.render_fwd(cam, pre, ranges, values)[3]
+    g = (smooth_upstream(cam) * (margin > 1.0)[None]).astype(np.float32)
+    ref = orc.render_bwd(cam, sc, pre, ranges, values, g, mode="f64")["dopacity_logits"].reshape(-1)
+    gpu = run_gpu(sc, cam, "sh3", 3, g, capacity=values.size)["grads"]["dopacity_logits"].reshape(-1)
+    a, b, c = pre["conic"]
+    error = np.median(np.abs(gpu - ref) / np.abs(ref) * (1 - b * b / (a * c)))
+    say("case thin opacity %dx%d: dopacity_logits error %.2e kappa" % (*size, error))
+    assert error <= 1.5 * 2.1e-8 / 2
+
+
 @pytest.mark.parametrize("n,tiles", [(1, (1, 1)), (127, (1, 1)), (255, (2, 1)), (256, (1, 2)), (257, (1, 1)),
                                      (1025, (2, 2)), (128, (32, 49)), (129, (39, 40)), (300, (40, 39))])
 def test_backward_spans(n, tiles):
