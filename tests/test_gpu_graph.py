@@ -52,9 +52,19 @@ def check_close(a, b, kind, label):
 
 @pytest.mark.parametrize("kind", ["sh3", "latent"])
 def test_step_in_a_graph(kind):
+    replays_match(kind, inputs.make_scene("medium", appearance=(kind,)), inputs.make_cameras("medium")[:3])
+
+
+@pytest.mark.parametrize("n,size", [(1024, (64, 64)), (12289, (330, 200)), (20001, (700, 560))])
+def test_few_gaussians_in_a_graph(n, size):
+    # the few-Gaussian binning (depths sorted in one workgroup, and by passes) and the
+    # blends with one and two pixels per lane
+    cams = [inputs.look_at_camera(p, *size) for p in ([0.0, 0.0, -3.0], [2.0, 1.0, -2.0])]
+    replays_match("sh3", inputs.make_scene("tiny", n=n), cams)
+
+
+def replays_match(kind, sc, cams):
     kid = {"sh3": gs.GS_APP_SH3, "latent": gs.GS_APP_LATENT_MLP}[kind]
-    sc = inputs.make_scene("medium", appearance=(kind,))
-    cams = inputs.make_cameras("medium")[:3]
     say("case graph %s: %d Gaussians, %d cameras" % (kind, sc.n, len(cams)))
     st = gs.SceneTensors(sc)
     cs = [gs.camera_struct(c) for c in cams]
